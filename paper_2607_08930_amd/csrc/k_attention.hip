@@ -21,8 +21,10 @@
 // registers, 8x8 bf16 blocks) so each lane reads its 8 keys of one feature
 // with two 8-byte LDS reads. Softmax statistics and accumulators are fp32.
 //
-// fp32 path: one wave per (request, query head, block row); lane t scores key
-// t of each 64-key chunk, the weights are broadcast by lane shuffles for P V.
+// fp32 path: matrix cores at D = 64, 128 and 256 (k_attn_f32_mfma); at other
+// head dimensions one wave per (request, query head, block row), where lane t
+// scores key t of each 64-key chunk and the weights are broadcast by lane
+// shuffles for P V.
 #include <float.h>
 
 #include "bs_internal.h"
@@ -119,6 +121,261 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a, int jblocks) {
     for (int d = lane; d < D; d += 64) {
       kcb[(int64_t)(bs + j) * D + d] = knb[(int64_t)j * fresh_stride + d];
       vcb[(int64_t)(bs + j) * D + d] = vnb[(int64_t)j * fresh_stride + d];
+    }
+  }
+}
+
+// fp32 on the matrix cores (D = 64, 128, 256): v_mfma_f32_16x16x4_f32, full
+// fp32 products and sums. One workgroup per (request, KV head, 32 query rows),
+// the rows of a KV head's query group counted as g * L + j. Its NW waves take
+// the row's 16-key tiles in turn (wave w tiles w, w + NW, ...), each with its
+// own LDS slots for one K and one V tile (direct DMA) and its own online
+// softmax, so the loop has no barrier; the waves' partials are combined
+// through LDS at the end. A wave refills its K slot as soon as its scores are
+// out and its V slot after P V, and the two waves of a SIMD fill each other's
+// waits.
+// S^T = K Q^T: lane (q, n) = (lane / 16, lane % 16) reads feature chunk
+// 16 c + 4 q .. + 3 of key n, which feeds four MFMAs (the contraction order is
+// free); the result leaves it with keys 4 q .. + 3 of query column n, which are
+// the B operands of O^T += V^T P^T as they stand (MFMA r contracts keys
+// 4 q + r). A lane's V read of 4 consecutive features likewise feeds four
+// MFMAs, so their M index m stands for feature 64 dg + 4 m + e.
+// Bound: HBM (K and V are read once per 32 query rows) with the fp32 matrix
+// rate, a sixteenth of bf16's, close behind. Measured on 8 LLaDA-8B-shaped
+// requests (32 heads, up to 733 keys, 135 MB): 46.5 us, 2.9 TB/s, against
+// 778 us for the one-wave-per-row kernel above; four waves with two stages of
+// both tiles each, 55 us.
+
+// exp(x) for x <= about 88 from the hardware's exp2: the rounding of
+// x log2(e) and of log2(e) itself comes back as a first-order factor, so the
+// error stays near one ulp of the result for large |x| too. Arguments below
+// -200 (and -inf) give 0.
+__device__ inline float exp_f32(float x) {
+  constexpr float kL2eHi = 1.44269502e+0f, kL2eLo = 1.92596299e-8f, kLn2 = 0.6931471805599453f;
+  x = fmaxf(x, -200.0f);
+  const float h = x * kL2eHi;
+  const float lo = fmaf(x, kL2eLo, fmaf(x, kL2eHi, -h));
+  const float e = __builtin_amdgcn_exp2f(h);
+  return fmaf(e, lo * kLn2, e);
+}
+
+// lanes l, l ^ 16, l ^ 32 and l ^ 48 combined through the VALU's row and half
+// swaps (no LDS round trip)
+__device__ inline float quarter_max(float v) {
+  auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+  p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+
+template <int D, int NT, int NW>
+__global__ __launch_bounds__(64 * NW, NW / 4) void k_attn_f32_mfma(AttnArgs a, int rtiles) {
+  constexpr int KT = 16;                          // keys per tile
+  constexpr int NC = D / 16;                      // 16-feature chunks of the score contraction
+  constexpr int NDG = D / 64;                     // 64-feature groups of the output
+  constexpr int NCH = D / 4;                      // 16-byte chunks per row
+  constexpr int TILE = KT * D;                    // floats of one K (or V) tile
+  constexpr int TB = TILE * 4 / 1024;             // 1 KiB DMA blocks per tile
+  __shared__ __align__(1024) float lds[NW * 2 * TILE];
+  __shared__ float sml[2][NW][16 * NT];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int q = lane >> 4, n = lane & 15;
+  const int rt = blockIdx.x % rtiles, ic = blockIdx.x / rtiles;
+  const int c = ic % a.Hkv, i = ic / a.Hkv;
+  const bs_req_desc rq = a.reqs[i];
+  const Geo geo = geo_of(rq, a.L);
+  const int bs = geo.s, be = geo.s + geo.B, len = geo.len;
+  const int64_t cache_off = (((int64_t)rq.row * a.Hkv + c) * a.W + rq.off) * D;
+  const int64_t fstride = (int64_t)a.Hkv * D;
+  const float* kcb = static_cast<const float*>(a.k_cache) + cache_off;
+  const float* vcb = static_cast<const float*>(a.v_cache) + cache_off;
+  const float* knb = static_cast<const float*>(a.k_new) + ((int64_t)i * a.L * a.Hkv + c) * D;
+  const float* vnb = static_cast<const float*>(a.v_new) + ((int64_t)i * a.L * a.Hkv + c) * D;
+
+  // XOR swizzle: 16 consecutive rows put one chunk in 16 distinct slots of the
+  // 256 bytes the LDS serves per cycle (K reads); a V read takes 16 consecutive
+  // chunks of one row.
+  float* slots = lds + w * 2 * TILE;              // this wave's K slot, then its V slot
+  const uint32_t slots_lds = lds_addr(slots);
+  // K (tensor 0) or V (1) of this wave's it-th tile
+  auto issue = [&](int tensor, int it) {
+    const int tb = (w + it * NW) * KT;
+    const bool whole = tb + KT <= len && (tb + KT <= bs || tb >= be);
+    const float* cb = tensor ? vcb : kcb;
+    const float* nb = tensor ? vnb : knb;
+#pragma unroll
+    for (int blk = 0; blk < TB; ++blk) {
+      const int u = blk * 64 + lane;                          // 16-byte slot of the tile
+      const int row = u / NCH, chunk = (u % NCH) ^ (row & 15);
+      const uint32_t dst = slots_lds + (uint32_t)(tensor * TILE * 4 + blk * 1024);
+      if (whole) {
+        dma16_sv_once(dst, uniform64(cb + (int64_t)tb * D), (uint32_t)(row * D + chunk * 4) * 4u);
+      } else {
+        const int t = min(tb + row, len - 1);                 // rows past the end repeat a valid key (masked later)
+        dma16_once(dst, (t >= bs && t < be ? nb + (int64_t)(t - bs) * fstride : cb + (int64_t)t * D) + chunk * 4);
+      }
+    }
+  };
+  const int ntiles = (len + KT - 1) / KT;
+  const int nt_w = w < ntiles ? (ntiles - w + NW - 1) / NW : 0;   // this wave's tiles
+  if (nt_w > 0) {
+    issue(0, 0);
+    issue(1, 0);
+  }
+
+  // queries: column n of n-tile t is row (16 NT) rt + 16 t + n of the group
+  f32x4_t qr[NT][NC];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int r = rt * 16 * NT + 16 * t + n;
+    const int g = r / a.L, j = r - g * a.L;
+    const bool ok = g < a.G && j < geo.B;
+    const float* qp = static_cast<const float*>(a.q) +
+                      (((int64_t)i * a.L + (ok ? j : 0)) * a.Hq + c * a.G + (ok ? g : 0)) * D;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      qr[t][k] = *reinterpret_cast<const f32x4_t*>(qp + 16 * k + 4 * q);
+      if (!ok) qr[t][k] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+  }
+  f32x4_t o[NT][NDG][4];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int dg = 0; dg < NDG; ++dg)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[t][dg][e] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  float mrun[NT], lsum[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    mrun[t] = -__builtin_inff();
+    lsum[t] = 0.0f;
+  }
+  // every LDS read of a slot has returned before its refill is issued
+  auto reads_done = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+  for (int it = 0; it < nt_w; ++it) {
+    const bool more = it + 1 < nt_w;
+    wait_vm_c<TB>();                              // K of this tile landed; its V may be in flight
+    asm volatile("" ::: "memory");
+    const float* kt = slots;
+    const float* vt = slots + TILE;
+    const int tb = (w + it * NW) * KT;
+    f32x4_t s[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) s[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      const f32x4_t kf = *reinterpret_cast<const f32x4_t*>(kt + n * D + (((4 * k + q) ^ n) * 4));
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qr[t][k][e], s[t], 0, 0, 0);
+    }
+    reads_done();
+    if (more) issue(0, it + 1);
+    // lane (q, n) holds S^T[key 4 q + r][query n]
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s[t][r] *= a.scale;
+      if (tb + KT > len) {                        // ragged last tile only
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (tb + 4 * q + r >= len) s[t][r] = -__builtin_inff();
+      }
+      const float mx = quarter_max(fmaxf(fmaxf(s[t][0], s[t][1]), fmaxf(s[t][2], s[t][3])));
+      // lazy rescale: the reference max moves only when a score exceeds it by
+      // 8 (the tile holds at least one key, so mx is finite)
+      if (__builtin_amdgcn_ballot_w64(mx > mrun[t] + 8.0f)) {
+        const float mnew = fmaxf(mrun[t], mx);
+        const float alpha = exp_f32(mrun[t] - mnew);
+        lsum[t] *= alpha;
+#pragma unroll
+        for (int dg = 0; dg < NDG; ++dg)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[t][dg][e] *= alpha;
+        mrun[t] = mnew;
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[t][r] = exp_f32(s[t][r] - mrun[t]);
+        lsum[t] += s[t][r];
+      }
+    }
+    if (more)
+      wait_vm_c<TB>();                            // V landed; the next K may be in flight
+    else
+      wait_vm_c<0>();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int dg = 0; dg < NDG; ++dg)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 4 * q + r;
+        const f32x4_t vf = *reinterpret_cast<const f32x4_t*>(vt + row * D + (((16 * dg + n) ^ row) * 4));
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+            o[t][dg][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e], s[t][r], o[t][dg][e], 0, 0, 0);
+      }
+    reads_done();
+    if (more) issue(1, it + 1);
+  }
+  // combine the waves: weights exp(m_w - M), then the sum of their outputs.
+  // Lane (q, n), register (dg, e, r): feature 64 dg + 16 q + 4 r + e of query n.
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    float l = lsum[t] + __shfl_xor(lsum[t], 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    if (q == 0) {
+      sml[0][w][16 * t + n] = mrun[t];
+      sml[1][w][16 * t + n] = l;
+    }
+  }
+  __syncthreads();
+  static_assert(16 * NT * D <= 2 * TILE, "a wave's partial output fits its slots");
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    float M = sml[0][0][16 * t + n];
+#pragma unroll
+    for (int k = 1; k < NW; ++k) M = fmaxf(M, sml[0][k][16 * t + n]);
+    float l = 0.0f;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) l += sml[1][k][16 * t + n] * exp_f32(sml[0][k][16 * t + n] - M);
+    const float wgt = exp_f32(mrun[t] - M) / l;   // 0 for a wave without tiles (mrun = -inf)
+#pragma unroll
+    for (int dg = 0; dg < NDG; ++dg)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const f32x4_t x = {o[t][dg][0][r] * wgt, o[t][dg][1][r] * wgt, o[t][dg][2][r] * wgt, o[t][dg][3][r] * wgt};
+        *reinterpret_cast<f32x4_t*>(slots + (16 * t + n) * D + (((16 * dg + 4 * q + r) ^ n) * 4)) = x;
+      }
+  }
+  __syncthreads();
+  for (int u = threadIdx.x; u < 16 * NT * NCH; u += 64 * NW) {
+    const int rl = u / NCH, ch = u % NCH;
+    const int r = rt * 16 * NT + rl;
+    const int g = r / a.L, j = r - g * a.L;
+    if (g >= a.G) continue;
+    f32x4_t x = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (j < geo.B) {
+#pragma unroll
+      for (int k = 0; k < NW; ++k)
+        x += *reinterpret_cast<const f32x4_t*>(lds + k * 2 * TILE + rl * D + ((ch ^ (rl & 15)) * 4));
+    }
+    float* op = static_cast<float*>(a.out) + (((int64_t)i * a.L + j) * a.Hq + c * a.G + g) * D;
+    __builtin_nontemporal_store(x, reinterpret_cast<f32x4_t*>(op + ch * 4));
+  }
+  if (a.write_back && rt == 0) {
+    float* kcw = static_cast<float*>(a.k_cache) + cache_off + (int64_t)bs * D;
+    float* vcw = static_cast<float*>(a.v_cache) + cache_off + (int64_t)bs * D;
+    for (int u = threadIdx.x; u < geo.B * NCH; u += 64 * NW) {
+      const int j = u / NCH, ch = u % NCH;
+      *reinterpret_cast<f32x4_t*>(kcw + (int64_t)j * D + ch * 4) =
+          *reinterpret_cast<const f32x4_t*>(knb + (int64_t)j * fstride + ch * 4);
+      *reinterpret_cast<f32x4_t*>(vcw + (int64_t)j * D + ch * 4) =
+          *reinterpret_cast<const f32x4_t*>(vnb + (int64_t)j * fstride + ch * 4);
     }
   }
 }
@@ -843,7 +1100,27 @@ hipError_t launch_bf16_d(const AttnArgs& a, int GW, hipStream_t s) {
 
 }  // namespace
 
+namespace {
+template <int D, int NW>
+hipError_t launch_f32_d(const AttnArgs& a, int n_req, hipStream_t s) {
+  const int rows = a.G * a.L;
+  const int rtiles = rows <= 16 ? 1 : (rows + 31) / 32;
+  const dim3 grid((unsigned)((int64_t)n_req * a.Hkv * rtiles)), block(64 * NW);
+  if (rows <= 16)
+    hipLaunchKernelGGL((k_attn_f32_mfma<D, 1, NW>), grid, block, 0, s, a, rtiles);
+  else
+    hipLaunchKernelGGL((k_attn_f32_mfma<D, 2, NW>), grid, block, 0, s, a, rtiles);
+  return hipGetLastError();
+}
+}  // namespace
+
+// Head dimensions the matrix-core kernel is laid out for go to it (at D = 256
+// four waves' slots fill the LDS, and a wave needs more than half a SIMD's
+// registers). The others keep the one-wave-per-row kernel.
 hipError_t launch_attn_f32(const AttnArgs& a, int n_req, hipStream_t s) {
+  if (a.D == 64) return launch_f32_d<64, 8>(a, n_req, s);
+  if (a.D == 128) return launch_f32_d<128, 8>(a, n_req, s);
+  if (a.D == 256) return launch_f32_d<256, 4>(a, n_req, s);
   const int jblocks = (a.L + 3) / 4;
   const dim3 grid((unsigned)((int64_t)n_req * a.Hq * jblocks)), block(256);
   hipLaunchKernelGGL(k_attn_f32, grid, block, 0, s, a, jblocks);

@@ -383,6 +383,21 @@ def test_attention_group_ring_phases(ctx, Hq, Hkv, D):
     _att(ctx, at_start, f"G{Hq // Hkv} D{D} block first")
 
 
+@pytest.mark.parametrize("L,Hq,Hkv,D", [(8, 2, 2, 64), (5, 6, 2, 64), (24, 3, 3, 128), (9, 14, 2, 128),
+                                        (64, 2, 1, 128), (16, 1, 1, 256), (33, 2, 2, 256)])
+def test_attention_fp32_matrix_tiles(ctx, L, Hq, Hkv, D):
+    # the fp32 matrix-core kernel deals a row's 16-key tiles to its 2 or 4
+    # waves: rows from one key to several tiles per wave, whole and ragged,
+    # with the fresh block last and first, and query groups (g * L + j) of one
+    # 16-row tile, of 32-row tiles with a remainder, and of several tiles
+    lens = [1, 2, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 160, 193]
+    at_end = synth.custom(L, Hq, Hkv, D, 10, "f32", [max(t - L, 0) for t in lens], [min(t, L) for t in lens],
+                          [0] * len(lens), q_sigma=2.0)
+    at_start = synth.custom(L, Hq, Hkv, D, 10, "f32", [0] * len(lens), lens, [0] * len(lens), variant=1)
+    _att(ctx, at_end, f"fp32 L{L} G{Hq // Hkv} D{D} block last")
+    _att(ctx, at_start, f"fp32 L{L} G{Hq // Hkv} D{D} block first")
+
+
 def test_attention_long_rows(ctx):
     # rows far longer than the workloads': 16 384 keys for MHA (512 tiles of a
     # single wave's stream) and 12 000 for a 7-head group, next to short rows
