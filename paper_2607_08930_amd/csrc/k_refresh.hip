@@ -18,11 +18,17 @@
 //                per SIMD), so one workgroup's prologue (first tiles, queries
 //                and their rotation) runs beside the other's loop. K/V tiles
 //                of 32 keys stream HBM/L2 -> LDS by direct DMA through a
-//                5-stage ring, two tiles in flight. Inside a wave the loop is
-//                software-pipelined by
+//                4-stage ring. Inside a wave the loop is software-pipelined by
 //                32-key sub-tiles: while the exponentials of sub-tile u run on
-//                the VALU, the matrix core computes the scores of u + 1 and
-//                accumulates P V of u - 1.
+//                the VALU, the matrix core accumulates P V of u - 1 and
+//                computes the scores of u + 1. Four sub-tiles are unrolled
+//                over the ring's slots, so LDS addresses are immediates and a
+//                sub-tile is 16 MFMAs beside 59 VALU instructions. What bounds
+//                it: MFMA and VALU issue (matrix cores busy 46% at 2.1 GHz).
+//                Measured on 64 Dream-7B-shaped rows (1.21 TFLOP): 1215 us in
+//                steady state, 1000 TFLOP/s; with per-sub-tile address
+//                arithmetic (about 40 VALU instructions more) and V fragments
+//                read right before their MFMA, 1.11x the whole call's time.
 #include "bs_lds.h"
 #include "bs_refresh.h"
 
@@ -37,8 +43,9 @@ typedef __attribute__((address_space(3))) bf16x4_t lds_bf16x4;
 
 __device__ inline float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ inline float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
 __device__ inline uint32_t pack_bf16(float lo, float hi) {
-  return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)lo) | ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)hi) << 16);
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, bf16x2_t));
 }
 
 // Rotate the feature pairs (x1[e], x2[e]) of 8 consecutive features f0 .. f0+7
@@ -111,16 +118,21 @@ __device__ inline float add_weights(float lsum, const bf16x8_t& p) {
   return lsum;
 }
 
-// NW waves of QW 32-query blocks each (NW * QW * 32 = 256 queries per
-// workgroup) share the K/V ring. QW = 2 feeds every LDS fragment to two
-// MFMAs but needs about 400 registers (one wave per SIMD, so nothing hides
-// the softmax arithmetic and the LDS latency: 20% slower on the Dream-7B
-// shape); QW = 1 reads twice the LDS bytes per MFMA and fits two waves per
-// SIMD (222 VGPRs), which is what the launch uses.
-template <int D, int QW, int NW>
+// compile-time integer passed to a generic lambda
+template <int V>
+struct Const {
+  static constexpr int value = V;
+  __device__ constexpr operator int() const { return V; }
+};
+
+// NW waves of 32 queries each share the K/V ring. Two 32-query blocks per wave
+// would feed every LDS fragment to two MFMAs but need about 400 registers (one
+// wave per SIMD, so nothing hides the softmax arithmetic and the LDS latency:
+// 20% slower on the Dream-7B shape).
+template <int D, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void k_refresh_attn(RefArgs a) {
   static_assert(D == 128, "the refresh attention is laid out for D = 128");
-  static_assert(NW * QW * 32 == kRefQ, "a workgroup covers kRefQ queries");
+  static_assert(NW * 32 == kRefQ, "a workgroup covers kRefQ queries");
   constexpr int KT = kRefKT, NS = kRefNS;
   constexpr int NKK = D / 16;        // K-steps of a score MFMA
   constexpr int NDT = D / 32;        // 32-feature output tiles
@@ -137,7 +149,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_refresh_attn(RefArgs a) {
   const int lane = threadIdx.x & 63, g = lane >> 5, n = lane & 31;
   const int len = it.len, h = it.h, c = h / a.G;
   const int ntiles = (len + KT - 1) / KT, nsub = (len + 31) / 32;
-  const int qbase = it.q0 + 32 * QW * w;             // first query of this wave
+  const int qbase = it.q0 + 32 * w;             // first query of this wave
   const bool active = qbase < len;                   // wave-uniform
 
   const int64_t cache_off = (((int64_t)it.row * a.Hkv + c) * a.W + it.off) * D;
@@ -150,9 +162,11 @@ __global__ __launch_bounds__(64 * NW, 2) void k_refresh_attn(RefArgs a) {
   // slot ^ swz(row).
   const int tensor = w / WPT;
   const uint16_t* tb_src = tensor ? vcb : kcb;
-  const uint32_t ring_lds = lds_addr(ring);
-  auto issue = [&](int tile) {
-    const uint32_t sbase = __builtin_amdgcn_readfirstlane(ring_lds + (uint32_t)((tile % NS) * STAGE * 2));
+  // the ring holds NS K tiles, then NS V tiles, so that every LDS read is a
+  // lane offset plus an immediate below 64 KiB
+  const uint32_t ring_lds = __builtin_amdgcn_readfirstlane(lds_addr(ring) + (uint32_t)(tensor * NS * TILE * 2));
+  auto issue = [&](int tile, int slot) {
+    const uint32_t sbase = ring_lds + (uint32_t)(slot * TILE * 2);
     const int t0 = tile * KT;
     if (t0 + KT <= len) {
       const uint64_t base = uniform64(tb_src + (int64_t)t0 * D);
@@ -161,7 +175,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_refresh_attn(RefArgs a) {
         const int rb = (w % WPT) * PB + k;
         const int row = rb * 4 + (lane >> 4);
         const int chunk = (lane & 15) ^ swz16(row);
-        dma16_sv(sbase + (uint32_t)((tensor * TILE + rb * 4 * D) * 2), base, (uint32_t)(row * D + chunk * 8) * 2u);
+        dma16_sv(sbase + (uint32_t)(rb * 4 * D * 2), base, (uint32_t)(row * D + chunk * 8) * 2u);
       }
     } else {
       // ragged last tile: rows past the row end repeat its last key (masked)
@@ -171,23 +185,23 @@ __global__ __launch_bounds__(64 * NW, 2) void k_refresh_attn(RefArgs a) {
         const int row = rb * 4 + (lane >> 4);
         const int chunk = (lane & 15) ^ swz16(row);
         const int t = min(t0 + row, len - 1);
-        dma16(sbase + (uint32_t)((tensor * TILE + rb * 4 * D) * 2), tb_src + (int64_t)t * D + chunk * 8);
+        dma16(sbase + (uint32_t)(rb * 4 * D * 2), tb_src + (int64_t)t * D + chunk * 8);
       }
     }
   };
 
   // prologue: tiles 0 .. 2 in flight before the queries load
-  issue(0);
-  if (ntiles > 1) issue(1);
-  if (ntiles > 2) issue(2);
+  // (the V waves run one tile behind the K waves, as in the loop)
+  issue(0, 0);
+  if (ntiles > 1) issue(1, 1);
+  if (ntiles > 2 && tensor == 0) issue(2, 2);
 
   // queries of this lane's column n of each query block, rotated, as MFMA B
   // operands: feature 16 kk + 8 g + e; the rotation partner of kk < NKK/2 is
   // chunk kk + NKK/2 of the same lane
-  bf16x8_t qb[QW][NKK];
-#pragma unroll
-  for (int b = 0; b < QW; ++b) {
-    const int j = min(qbase + 32 * b + n, len - 1);
+  bf16x8_t qb[NKK];
+  {
+    const int j = min(qbase + n, len - 1);
     const uint16_t* qp = a.q + (((int64_t)it.row * a.W + it.off + j) * a.Hq + h) * D;
     v4u x[NKK];
 #pragma unroll
@@ -197,230 +211,215 @@ __global__ __launch_bounds__(64 * NW, 2) void k_refresh_attn(RefArgs a) {
       for (int kk = 0; kk < NKK / 2; ++kk) rope8(x[kk], x[kk + NKK / 2], 16 * kk + 8 * g, (float)j, a.nl2b);
     }
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) qb[b][kk] = __builtin_bit_cast(bf16x8_t, x[kk]);
+    for (int kk = 0; kk < NKK; ++kk) qb[kk] = __builtin_bit_cast(bf16x8_t, x[kk]);
   }
 
-  // loop-invariant LDS element offsets of this lane's K and V fragments
+  // loop-invariant LDS byte offsets of this lane's K and V fragments (V rows
+  // 16 apart have the same swizzle, so the K-step ks is a constant offset)
   int koff[NKK];
 #pragma unroll
-  for (int kk = 0; kk < NKK; ++kk) koff[kk] = n * D + (((2 * kk + g) ^ swz16(n)) * 8);
+  for (int kk = 0; kk < NKK; ++kk) koff[kk] = (n * D + (((2 * kk + g) ^ swz16(n)) * 8)) * 2;
   const int q16 = lane >> 4, j16 = lane & 15;
   const int vrow = 4 * (q16 >> 1) + (j16 >> 2);
-  int voff[NDT][2][2];
+  int voff[NDT][2];
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2) {
-        const int row = 16 * ks + 8 * h2 + vrow;
-        const int col = 32 * dt + 16 * (q16 & 1) + 4 * (j16 & 3);
-        voff[dt][ks][h2] = row * D + (((col >> 3) ^ swz16(row)) * 8) + (col & 7);
-      }
+    for (int h2 = 0; h2 < 2; ++h2) {
+      const int row = 8 * h2 + vrow;
+      const int col = 32 * dt + 16 * (q16 & 1) + 4 * (j16 & 3);
+      voff[dt][h2] = (NS * TILE + row * D + (((col >> 3) ^ swz16(row)) * 8) + (col & 7)) * 2;
+    }
 
-  f32x16_t o[QW][NDT];
+  f32x16_t o[NDT];
 #pragma unroll
-  for (int b = 0; b < QW; ++b)
+  for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-      for (int rr = 0; rr < 16; ++rr) o[b][dt][rr] = 0.0f;
-  float mrun[QW], lsum[QW], alpha_pend[QW];
-#pragma unroll
-  for (int b = 0; b < QW; ++b) {
-    mrun[b] = -__builtin_inff();
-    lsum[b] = 0.0f;
-    alpha_pend[b] = 1.0f;
-  }
-  bool resc_pend = false;
+    for (int rr = 0; rr < 16; ++rr) o[dt][rr] = 0.0f;
+  float mrun = -__builtin_inff(), mtop = -__builtin_inff(), lsum = 0.0f, alpha = 1.0f;   // mtop = mrun + 8
 
-  // K rows of sub-tile u (32 keys) start at element sub_k(u); its V rows at + TILE
-  auto sub_k = [&](int u) { return ((u / SPT) % NS) * STAGE + (u % SPT) * 32 * D; };
-  auto vfrag = [&](const uint16_t* vs, int dt, int ks) {
-    const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(vs + voff[dt][ks][0]));
-    const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(vs + voff[dt][ks][1]));
+  // operand fragments of the K and V tiles in a slot (i = 4 ks + dt)
+  auto kfrag = [&](int slot, int kk) {
+    return *reinterpret_cast<const bf16x8_t*>(reinterpret_cast<const char*>(ring) + koff[kk] + slot * TILE * 2);
+  };
+  auto vfrag = [&](int slot, int i) {
+    const char* vs = reinterpret_cast<const char*>(ring) + slot * TILE * 2 + (i >> 2) * 16 * D * 2;
+    const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(vs + voff[i & 3][0]));
+    const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(vs + voff[i & 3][1]));
     return (bf16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
   auto rescale = [&]() {
 #pragma unroll
-    for (int b = 0; b < QW; ++b)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-        for (int rr = 0; rr < 16; ++rr) o[b][dt][rr] *= alpha_pend[b];
+      for (int rr = 0; rr < 16; ++rr) o[dt][rr] *= alpha;
+  };
+  // x is computed here: keeps the compiler from sinking it past a fence
+  auto pin = [](float& x) { asm volatile("" : "+v"(x)); };
+  auto barrier = [] {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
   };
 
-  // tile 0 landed (tiles 1, 2 may still be in flight), visible to all waves
-  if (ntiles > 2)
-    wait_vm_c<2 * PB>();
-  else if (ntiles > 1)
-    wait_vm_c<PB>();
-  else
-    wait_vm_c<0>();
-  __syncthreads();
+  // K tile 0 landed (K tiles 1 and 2 may still be in flight), visible to all
+  // waves; the loop waits for V
+  if (tensor == 0) {
+    if (ntiles > 2)
+      wait_vm_c<2 * PB>();
+    else if (ntiles > 1)
+      wait_vm_c<PB>();
+    else
+      wait_vm_c<0>();
+  }
+  barrier();
 
-  // two sets of score and probability registers, used in turn by the two
-  // halves of each loop trip (no register copies between sub-tiles)
-  f32x16_t sA[QW], sB[QW];
-  bf16x8_t pA[QW][2], pB[QW][2];
-#pragma unroll
-  for (int b = 0; b < QW; ++b)
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) pA[b][ks][e] = (__bf16)0.0f;
+  // two sets of score registers, used in turn by the two halves of each loop
+  // trip; one set of probabilities
+  f32x16_t sA, sB;
+  bf16x8_t pp[2];
+  bf16x8_t fr[4];                                    // operand fragments read three MFMAs ahead
   if (active) {
 #pragma unroll
-    for (int b = 0; b < QW; ++b)
+    for (int rr = 0; rr < 16; ++rr) sA[rr] = 0.0f;
 #pragma unroll
-      for (int rr = 0; rr < 16; ++rr) sA[b][rr] = 0.0f;
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
-      const bf16x8_t kf = *reinterpret_cast<const bf16x8_t*>(ring + koff[kk]);
-#pragma unroll
-      for (int b = 0; b < QW; ++b) sA[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qb[b][kk], sA[b], 0, 0, 0);
-    }
+    for (int kk = 0; kk < NKK; ++kk) sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag(0, kk), qb[kk], sA, 0, 0, 0);
   }
 
-  // one sub-tile u: sc holds its scores, pprev the probabilities of u - 1;
-  // writes the scores of u + 1 to sn and the probabilities of u to pcur
-  auto sub_tile = [&](int u, f32x16_t (&sc)[QW], f32x16_t (&sn)[QW], const bf16x8_t (&pprev)[QW][2],
-                      bf16x8_t (&pcur)[QW][2]) {
-    const int un = u + 1;
-    if (un < nsub && un % SPT == 0) {
-      // sub-tile un opens tile T: it has landed once only tile T + 1 (if
-      // issued) is in flight. Tile T + 2 refills the slot of tile T + 2 - NS;
-      // P V runs one sub-tile behind the scores, so this step still reads V
-      // of sub-tile T SPT - 2, in tile T - ceil(2 / SPT): the refilled tile
-      // must be older than that.
-      static_assert(NS >= 3 + (SPT + 1) / SPT, "ring too short for the lagging P V");
-      const int T = un / SPT;
-      if (T + 1 < ntiles)
-        wait_vm_c<PB>();
-      else
-        wait_vm_c<0>();
-      __syncthreads();
-      if (T + 2 < ntiles) issue(T + 2);
+  // one sub-tile u in ring slot S = u % NS (compile time in the unrolled loop,
+  // where every LDS address is then an immediate): sc holds its scores, pp the
+  // probabilities of u - 1; writes the scores of u + 1 to sn and the
+  // probabilities of u to pp. Sixteen slots of one MFMA each, in an order fixed
+  // by scheduling fences: P V of u - 1 (nothing for the first sub-tile), then
+  // the scores of u + 1 (of stale LDS contents and discarded for the last);
+  // beside them the max, the exponentials, their conversion and sum. Every
+  // MFMA's LDS operand is read three MFMAs before it.
+  auto sub_tile = [&](auto slot, auto first_tag, int u, f32x16_t& sc, f32x16_t& sn) {
+    constexpr bool FIRST = decltype(first_tag)::value;
+    const int S = slot, vprev = (slot + NS - 1) % NS, knext = (slot + 1) % NS;
+    // K tile u + 1 and V tile u have landed once only one later tile of each
+    // (if issued) is in flight. Past the barrier every wave is done with K of
+    // u - 1 .. u and V of u - 2, whose slots take K of u + 3 and V of u + 2.
+    static_assert(NS == 4 && SPT == 1, "K of u + 3 refills the slot of u - 1, V of u + 2 that of u - 2");
+    if (tensor == 0 ? u + 2 < ntiles : u + 1 < ntiles)
+      wait_vm_c<PB>();
+    else
+      wait_vm_c<0>();
+    barrier();
+    if (tensor == 0) {
+      if (u + 3 < ntiles) issue(u + 3, (slot + 3) % NS);
+    } else {
+      if (u + 2 < ntiles) issue(u + 2, (slot + 2) % NS);
     }
     if (!active) return;
-    // a reference max raised in the previous sub-tile rescales the
-    // accumulators now, after P V of its predecessor and before its own (at
-    // the top, so the tail stays one basic block in which the exponentials
-    // and the MFMAs can interleave)
-    if (resc_pend) {
-      rescale();
-      resc_pend = false;
-    }
-    // K fragments of sub-tile u + 1 (on the last sub-tile a resident one
-    // again, its scores discarded), issued first so their latency hides under
-    // the softmax arithmetic; V of u - 1 (of sub-tile 0 at u = 0, with zero
-    // weights)
-    const uint16_t* kt = ring + sub_k(un < nsub ? un : u);
-    const uint16_t* vs = ring + sub_k(u > 0 ? u - 1 : 0) + TILE;
-    bf16x8_t kf[NKK];
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) kf[kk] = *reinterpret_cast<const bf16x8_t*>(kt + koff[kk]);
     const int k0 = u * 32;
     if (k0 + 32 > len) {                               // ragged last sub-tile
 #pragma unroll
       for (int rr = 0; rr < 16; ++rr) {
         const int key = k0 + 8 * (rr >> 2) + 4 * g + (rr & 3);
-        if (key >= len) {
+        if (key >= len) sc[rr] = -__builtin_inff();
+      }
+    }
+    float m3[4];
+    float mx = 0.0f;
+    bool resc = false;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int b = 0; b < QW; ++b) sc[b][rr] = -__builtin_inff();
+    for (int i = 0; i < 16; ++i) {
+      const int j = i + 3;
+      if (j >= 16)
+        fr[j & 3] = vfrag(S, j - 16);
+      else if (j >= 8)
+        fr[j & 3] = kfrag(knext, j - 8);
+      else if constexpr (!FIRST)
+        fr[j & 3] = vfrag(vprev, j);
+      if (i < 8) {
+        if constexpr (!FIRST)
+          o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i & 3], pp[i >> 2], o[i & 3], 0, 0, 0);
+      } else {
+        if (i == 8) {
+#pragma unroll
+          for (int rr = 0; rr < 16; ++rr) sn[rr] = 0.0f;
         }
+        sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i & 3], qb[i - 8], sn, 0, 0, 0);
       }
-    }
-    // running max per query (log2 units), lazily raised: the reference max
-    // moves only when a score exceeds it by 2^8, so the accumulators are
-    // rescaled a handful of times per row (alpha = 1 when it stays)
+      if (i == 1) {
 #pragma unroll
-    for (int b = 0; b < QW; ++b) {
-      float mx = vmax(sc[b][0], sc[b][1]);
-#pragma unroll
-      for (int rr = 2; rr < 16; ++rr) mx = vmax(mx, sc[b][rr]);
-      // the other half-wave holds the other 16 keys of this query
-      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-      mx = vmax(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * a.scale_log2e;
-      const bool resc = __builtin_amdgcn_ballot_w64(mx > mrun[b] + 8.0f) != 0;
-      const float mnew = resc ? fmaxf(mrun[b], mx) : mrun[b];
-      alpha_pend[b] = __builtin_amdgcn_exp2f(mrun[b] - mnew);
-      lsum[b] *= alpha_pend[b];
-      mrun[b] = mnew;
-      resc_pend |= resc;
-    }
-    // probabilities of sub-tile u on the VALU, interleaved with the matrix
-    // core's scores of u + 1 and P V of u - 1
-#pragma unroll
-    for (int b = 0; b < QW; ++b) {
-      const float nm = -mrun[b];
-#pragma unroll
-      for (int rr = 0; rr < 16; ++rr) {
-        const float pr = __builtin_amdgcn_exp2f(fmaf(sc[b][rr], a.scale_log2e, nm));
-        pcur[b][rr >> 3][rr & 7] = (__bf16)pr;
+        for (int r = 0; r < 4; ++r) {
+          m3[r] = vmax(vmax(sc[3 * r], sc[3 * r + 1]), sc[3 * r + 2]);
+          pin(m3[r]);
+        }
+      } else if (i == 2) {
+        m3[0] = vmax(vmax(sc[12], sc[13]), m3[0]);
+        m3[1] = vmax(vmax(sc[14], sc[15]), m3[1]);
+        m3[0] = vmax(vmax(m3[0], m3[1]), m3[2]);
+        mx = vmax(m3[0], m3[3]) * a.scale_log2e;       // log2 units
+        pin(mx);
+      } else if (i == 3) {
+        // lazily raised running max: the reference moves only when a score
+        // exceeds it by 2^8, so this branch is taken a handful of times per
+        // row; the other half-wave holds the other 16 keys of each query
+        resc = __builtin_amdgcn_ballot_w64(mx > mtop) != 0;
+        if (resc) {
+          const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+          const float mnew = fmaxf(mrun, vmax(__uint_as_float(sw[0]), __uint_as_float(sw[1])));
+          alpha = __builtin_amdgcn_exp2f(mrun - mnew);
+          lsum *= alpha;
+          mrun = mnew;
+          mtop = mnew + 8.0f;
+        }
+      } else if (i >= 4 && i < 12) {
+        const int e = 2 * (i - 4);
+        float y0 = __builtin_amdgcn_exp2f(fmaf(sc[e], a.scale_log2e, -mrun));
+        float y1 = __builtin_amdgcn_exp2f(fmaf(sc[e + 1], a.scale_log2e, -mrun));
+        pin(y0);
+        pin(y1);
+        sc[e] = y0;
+        sc[e + 1] = y1;
       }
-      lsum[b] = add_weights(add_weights(lsum[b], pcur[b][0]), pcur[b][1]);
-    }
-#pragma unroll
-    for (int b = 0; b < QW; ++b)
-#pragma unroll
-      for (int rr = 0; rr < 16; ++rr) sn[b][rr] = 0.0f;
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk)
-#pragma unroll
-      for (int b = 0; b < QW; ++b) sn[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qb[b][kk], sn[b], 0, 0, 0);
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const bf16x8_t va = vfrag(vs, dt, ks);
-#pragma unroll
-        for (int b = 0; b < QW; ++b)
-          o[b][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pprev[b][ks], o[b][dt], 0, 0, 0);
+      if (i >= 5 && i < 13) {
+        // P V has read this half of the old probabilities by now
+        const int e = 2 * (i - 5);
+        pp[e >> 3][e & 7] = (__bf16)sc[e];
+        pp[e >> 3][(e & 7) + 1] = (__bf16)sc[e + 1];
       }
-    // schedule: the max/rescale arithmetic, then one MFMA per few VALU ops
-    __builtin_amdgcn_sched_group_barrier(0x002, 20 * QW, 0);
-#pragma unroll
-    for (int i = 0; i < 16 * QW; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+      if (i == 9 || i == 13) {
+        lsum = add_weights(lsum, pp[i == 9 ? 0 : 1]);
+        pin(lsum);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (!FIRST && i == 7 && resc) rescale();         // after P V of u - 1, before that of u
     }
   };
 
-  int u = 0;
-  for (; u + 1 < nsub; u += 2) {
-    sub_tile(u, sA, sB, pA, pB);
-    sub_tile(u + 1, sB, sA, pB, pA);
+  // u = 0, then four sub-tiles per trip with compile-time slots, then the rest
+  sub_tile(Const<0>{}, Const<1>{}, 0, sA, sB);
+  int u = 1;
+  for (; u + 3 < nsub; u += 4) {
+    sub_tile(Const<1>{}, Const<0>{}, u, sB, sA);
+    sub_tile(Const<2>{}, Const<0>{}, u + 1, sA, sB);
+    sub_tile(Const<3>{}, Const<0>{}, u + 2, sB, sA);
+    sub_tile(Const<0>{}, Const<0>{}, u + 3, sA, sB);
   }
-  if (u < nsub) {                                   // odd count: the last sub-tile's probabilities end in pB
-    sub_tile(u, sA, sB, pA, pB);
-#pragma unroll
-    for (int b = 0; b < QW; ++b) {
-      pA[b][0] = pB[b][0];
-      pA[b][1] = pB[b][1];
-    }
+  int slot = 1;
+  for (; u + 1 < nsub; u += 2, slot += 2) {
+    sub_tile(slot, Const<0>{}, u, sB, sA);
+    sub_tile(slot + 1, Const<0>{}, u + 1, sA, sB);
   }
+  if (u < nsub) sub_tile(slot, Const<0>{}, u, sB, sA);
   if (!active) return;
-  if (resc_pend) rescale();
   {
-    const uint16_t* vs = ring + sub_k(nsub - 1) + TILE;
+    const int vs = (nsub - 1) % NS;                    // its first three fragments are read already
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const bf16x8_t va = vfrag(vs, dt, ks);
-#pragma unroll
-        for (int b = 0; b < QW; ++b)
-          o[b][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pA[b][ks], o[b][dt], 0, 0, 0);
-      }
+    for (int i = 0; i < 8; ++i)
+      o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(i < 3 ? fr[i] : vfrag(vs, i), pp[i >> 2], o[i & 3], 0, 0, 0);
   }
 
-  // lane (g, n): O^T[feature 32 dt + 8 (rr / 4) + 4 g + rr % 4][query n of block b]
+  // lane (g, n): O^T[feature 32 dt + 8 (rr / 4) + 4 g + rr % 4][query n]
   typedef uint32_t v2u __attribute__((ext_vector_type(2)));
-#pragma unroll
-  for (int b = 0; b < QW; ++b) {
-    const int j = qbase + 32 * b + n;
-    const float lt = lsum[b] + __shfl_xor(lsum[b], 32, 64);
+  {
+    const int j = qbase + n;
+    const float lt = lsum + __shfl_xor(lsum, 32, 64);
     if (j < len) {
       const float inv = 1.0f / lt;
       uint16_t* op = a.out + (((int64_t)it.row * a.W + it.off + j) * a.Hq + h) * D;
@@ -428,8 +427,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_refresh_attn(RefArgs a) {
       for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
         for (int rq = 0; rq < 4; ++rq) {
-          const uint32_t w0 = pack_bf16(o[b][dt][4 * rq + 0] * inv, o[b][dt][4 * rq + 1] * inv);
-          const uint32_t w1 = pack_bf16(o[b][dt][4 * rq + 2] * inv, o[b][dt][4 * rq + 3] * inv);
+          const uint32_t w0 = pack_bf16(o[dt][4 * rq + 0] * inv, o[dt][4 * rq + 1] * inv);
+          const uint32_t w1 = pack_bf16(o[dt][4 * rq + 2] * inv, o[dt][4 * rq + 3] * inv);
           *reinterpret_cast<v2u*>(op + dt * 32 + 8 * rq + 4 * g) = v2u{w0, w1};
         }
     }
@@ -447,8 +446,8 @@ hipError_t launch_refresh_kv(const RefKvArgs& a, int n, int max_len, hipStream_t
 }
 
 hipError_t launch_refresh_attn(const RefArgs& a, int n_items, hipStream_t s) {
-  constexpr int QW = 1, NW = kRefQ / (32 * QW);
-  hipLaunchKernelGGL((k_refresh_attn<128, QW, NW>), dim3((unsigned)n_items), dim3(64 * NW), 0, s, a);
+  constexpr int NW = kRefQ / 32;
+  hipLaunchKernelGGL((k_refresh_attn<128, NW>), dim3((unsigned)n_items), dim3(64 * NW), 0, s, a);
   return hipGetLastError();
 }
 

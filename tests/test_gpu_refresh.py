@@ -152,6 +152,31 @@ def test_random_geometries(ctx, seed):
         np.testing.assert_array_equal(vc_h[:, c][~used], vc[:, c][~used])
 
 
+def test_sub_tile_counts_with_moving_max(ctx):
+    # rows of 1 to 13 32-key sub-tiles, whole and ragged: the first sub-tile,
+    # trips of four with compile-time ring slots and every remainder behind
+    # them. Queries 40 times the usual size spread the scores over about +-12
+    # (log2 units), so the running maximum moves by more than its slack of 8
+    # inside rows and the accumulators are rescaled mid-loop. No rotation:
+    # queries and keys rounded after a rotation carry up to 2^-9 relative each,
+    # which at scores of standard deviation 3.5 is a score error near
+    # 3.5 sqrt(2) 2^-9 / sqrt(3) = 6e-3 and outputs 1-2% off, past the usual
+    # bound; unrotated inputs are exact and the usual bound holds.
+    torch, bs, bstep = lazy()
+    lens = [32 * m + d for m in range(1, 14) for d in (-31, 0) if (m + d) % 2 == 0 or m < 7]
+    w = synth.custom(32, 2, 1, 128, 10, "bf16", [0] * len(lens), lens, [0] * len(lens), variant=9,
+                     kv_sigma=1 / np.sqrt(128))
+    q, k, v = synth.gen_refresh(w)
+    q = synth.f32_to_bf16_bits(synth.bf16_bits_to_f32(q) * np.float32(40.0))
+    kc, vc = synth.poison_cache(w, *synth.gen_cache(w))
+    out, dkc, dvc = run_refresh(ctx, w, q, k, v, kc, vc, 0.0)
+    out_h, kc_h, vc_h = bstep.to_host(out), bstep.to_host(dkc), bstep.to_host(dvc)
+    for i, r in enumerate(w.reqs):
+        row, off, ln = int(r["row"]), int(r["off"]), int(r["p"] + r["g"])
+        check_request(w, i, out_h[row, off:off + ln], kc_h[row, :, off:off + ln], vc_h[row, :, off:off + ln],
+                      q, k, v, 0.0, label=f"{ln} keys")
+
+
 def test_rotation_disabled_copies_keys(ctx):
     torch, bs, bstep = lazy()
     w = small_workload(4, 2, variant=1)
