@@ -172,9 +172,8 @@ hipError_t launch_decode_marked(const DecArgs& a, bs_dtype dt, hipStream_t s, Ma
 // into one DecPartial per (row, 128-entry vocabulary slice), then merged into
 // the per-row part the selection reads.
 constexpr int kLmNT = 256;  // vocabulary entries per workgroup tile
-constexpr int kLmMT = 256;  // hidden rows per workgroup tile
+constexpr int kLmMT = 256;  // most hidden rows per workgroup tile
 constexpr int kLmKT = 32;   // reduction depth per LDS stage
-constexpr int kLmNS = 4;    // LDS stages
 
 inline int lm_parts(int V) { return 2 * ((V + kLmNT - 1) / kLmNT); }
 

@@ -12,11 +12,11 @@
 // k_lm_rows   one workgroup lists the masked rows (j < B_i, masked) of the
 //             compact [n][L] block state in increasing order and counts them.
 // k_lm_head   C^T = W H^T on v_mfma_f32_32x32x16_bf16 over 256 (vocabulary)
-//             x 256 (listed rows) tiles; K moves HBM -> LDS in 32-wide slices
-//             through a 4-deep ring by direct DMA. Vocabulary is the MFMA M
+//             x 64, 128, 192 or 256 (listed rows) tiles; K moves HBM -> LDS
+//             in 32-wide slices through a ring of 5 to 8 by direct DMA. Vocabulary is the MFMA M
 //             axis, so a lane holds one row's column of 16 logits per 32x32
-//             block: the epilogue reduces 64 logits per lane and exchanges
-//             once with the other half-wave. One DecPartial per (row,
+//             block: the epilogue reduces 32 logits per lane and row, exchanges
+//             once with the other half-wave and once through LDS. One DecPartial per (row,
 //             128-entry vocabulary slice).
 // k_lm_merge  one wave per listed row merges its slices into the DecPartial
 //             the selection reads.
@@ -63,152 +63,173 @@ __global__ __launch_bounds__(1024) void k_lm_rows(LmArgs a) {
 // LDS rows hold 32 bf16 of K (64 bytes, four 16-byte chunks). Chunk c of tile
 // row r sits in slot c ^ ((r >> 2) & 3): the 32 rows one MFMA operand read
 // touches then spread two per bank group.
-constexpr int kTile = kLmNT * kLmKT;        // elements of one operand tile (W or H): 16 KiB
-constexpr int kStage = 2 * kTile;           // W tile, then H tile
+constexpr int kTile = kLmNT * kLmKT;        // elements of the W tile of a stage: 16 KiB
+constexpr int kLdsBytes = 160 * 1024;       // all of a CU's LDS: one workgroup per CU
 
-__global__ __launch_bounds__(512, 1) void k_lm_head(LmArgs a) {
-  static_assert(kLmNT == 256 && kLmMT == 256 && kLmKT == 32 && kLmNS == 4, "tiling below assumes these");
-  __shared__ __align__(1024) uint16_t ring[kLmNS * kStage];   // 128 KiB
-  const int count = *a.count;
-  const int nvt = (a.V + kLmNT - 1) / kLmNT;
-  const int nrt = (a.n * a.L + kLmMT - 1) / kLmMT;
-  // Workgroups b = x + 8 q run on XCD x. With one or two row tiles in use,
-  // XCD x serves row tile x % nact only: that tile's hidden rows stay in its
-  // L2 while W streams past, and the XCDs serving a row tile split the
-  // vocabulary tiles round-robin (W is read once per row tile). With more
-  // row tiles, consecutive q on one XCD take all row tiles of one vocabulary
-  // tile, which then share that XCD's L2 copy of the W slab (W is read about
-  // once; the hidden rows come from L2 or the Infinity Cache). Measured on
-  // the LLaDA-8B and Dream-7B head shapes, each order is the faster one in
-  // its range.
-  if (count == 0) return;
-  const int x = (int)(blockIdx.x & 7), q = (int)(blockIdx.x >> 3);
-  const int nact = (count + kLmMT - 1) / kLmMT;
-  int vt, rt;
-  if (nact <= 2) {
-    rt = x % nact;
-    const int gsize = (8 - rt + nact - 1) / nact;
-    vt = q * gsize + x / nact;
-    if (vt >= nvt) return;
-  } else {
-    const int total = nvt * nrt, per_xcd = (total + 7) / 8;
-    const int lin = x * per_xcd + q;
-    if (q >= per_xcd || lin >= total) return;
-    vt = lin / nrt;
-    rt = lin - vt * nrt;
+template <int I>
+struct Const {
+  static constexpr int value = I;
+};
+
+// Wait until at most k (uniform, 0 <= k <= K) stages of C transfers each are
+// outstanding. In the loop k = K but for its last stages.
+template <int C, int K>
+__device__ inline void wait_stages(int k) {
+  if (k >= K) {
+    wait_vm_c<K * C>();
+  } else if constexpr (K > 0) {
+    wait_stages<C, K - 1>(k);
   }
-  const int v0 = vt * kLmNT, r0 = rt * kLmMT;
-  if (r0 >= count) return;
+}
+
+// One workgroup tile: 256 vocabulary entries x 64 M listed rows, M = 1..4.
+// Wave (wv, wr) = (w >> 1, w & 1) computes vocabulary rows 64 wv .. + 64 (two
+// 32-row blocks) x listed rows 32 M wr .. + 32 M.
+//
+// The matrix cores bound it, at the clock that their power leaves: the
+// operands of each half of a K slice (16 of its 32) are read from LDS beside
+// the MFMAs of the half before, and the slice's one barrier stands between the
+// halves, so that a wave leaves it with its next operands in registers and
+// the slot that the barrier frees is refilled at once. The order is fixed by
+// scheduling fences: one MFMA, then one LDS read or one transfer.
+// Measured on a Dream-7B head (V = 152064, d = 3584), 1035 listed rows: 1065 us,
+// MFMA busy 60% at 1.75 GHz. With a barrier before the reads of a whole slice
+// and five 256-row tiles the same rows took 1640 us.
+template <int M>
+__device__ inline void lm_tile(const LmArgs& a, uint16_t* ring, int vt, int r0, int count) {
+  constexpr int HB = 4 * M;                              // 1 KiB blocks (16 rows) of the H tile
+  constexpr int SLOT = kTile + HB * 512;                 // elements of a stage: W tile, then H tile
+  constexpr int NS = kLdsBytes / (SLOT * 2);             // 5 stages at M = 4, 8 at M = 1
+  constexpr int CHI = 2 + (HB + 7) / 8, CLO = 2 + HB / 8;   // transfers per stage of waves 0..3 and 4..7
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
 
-  // DMA: a stage is 32 blocks of 1 KiB (16 tile rows each); wave w issues
-  // blocks 4w .. 4w + 3: W rows for w < 4, H rows for w >= 4. Lane l fills
-  // slot l & 3 of tile row 16 b + (l >> 2) with global chunk
+  // DMA: wave w issues W blocks 2w and 2w + 1 and H blocks w and w + 8 (where
+  // the tile has them). W comes from the packed slabs (already in LDS order:
+  // a block is one contiguous KiB). H rows are gathered through the row list:
+  // lane l fills slot l & 3 of tile row 16 b + (l >> 2) with global chunk
   // (l & 3) ^ ((l >> 4) & 3).
-  const int gch = (lane & 3) ^ ((lane >> 4) & 3);
-  const bool wside = w < 4;
-  const int b0 = (w & 3) * 4;
-  // W comes from the packed slabs (already in LDS order: block b of slab
-  // (vt, t) is one contiguous KiB); H rows are gathered through the row list.
-  const uint16_t* hp[4];                       // H: listed row's K start + chunk
+  const uint16_t* hp[2];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int row = 16 * (b0 + q) + (lane >> 2);
-    hp[q] = wside ? nullptr : a.hidden + (int64_t)a.rows[min(r0 + row, count - 1)] * a.d + gch * 8;
+  for (int q = 0; q < 2; ++q) {
+    const int row = 16 * (w + 8 * q) + (lane >> 2);
+    hp[q] = a.hidden + (int64_t)a.rows[min(r0 + row, count - 1)] * a.d + ((lane & 3) ^ ((lane >> 4) & 3)) * 8;
   }
-  const uint32_t ring_lds = lds_addr(ring) + (uint32_t)((wside ? 0 : kTile * 2) + b0 * 1024);
-  const uint16_t* wslab = a.w + (int64_t)vt * (a.d / kLmKT) * kTile + b0 * 512;
-  // block q of this wave's share of stage t
-  auto issue1 = [&](int t, int q) {
-    const uint32_t sb = __builtin_amdgcn_readfirstlane(ring_lds + (uint32_t)((t % kLmNS) * kStage * 2));
-    if (wside)
-      dma16_sv(sb + q * 1024, uniform64(wslab + (int64_t)t * kTile + q * 512), (uint32_t)(lane * 16));
-    else
-      dma16(sb + q * 1024, hp[q] + t * kLmKT);
+  const uint32_t lds0 = lds_addr(ring);
+  const uint16_t* wp = a.w + (int64_t)vt * (a.d / kLmKT) * kTile + w * 1024;   // next stage to issue
+  uint32_t fill = lds0;                                                        // and its slot
+  auto issue_w = [&](int q) { dma16_sv(fill + (2 * w + q) * 1024, uniform64(wp + q * 512), (uint32_t)(lane * 16)); };
+  auto issue_h = [&](int q) {
+    if (HB >= 8 * (q + 1) || (HB > 8 * q && w < 4)) dma16(fill + kTile * 2 + (w + 8 * q) * 1024, hp[q]);
   };
-  auto issue = [&](int t) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) issue1(t, q);
+  auto issued = [&] {
+    wp += kTile;
+    hp[0] += kLmKT;
+    hp[1] += kLmKT;
+    fill = fill + SLOT * 2 == lds0 + NS * SLOT * 2 ? lds0 : fill + SLOT * 2;
+  };
+  auto wait_ahead = [&](int k) {
+    if (CHI == CLO || w < 4)
+      wait_stages<CHI, NS - 1>(k);
+    else
+      wait_stages<CLO, NS - 1>(k);
+  };
+  auto barrier = [] {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
   };
 
-  // MFMA operands: wave (wv, wr) = (w & 1, w >> 1) computes vocabulary rows
-  // 128 wv .. + 128 (four 32-row blocks) x hidden rows 64 wr .. + 64 (two).
-  // Lane (g, n) reads row n of a block, chunk 2 s + g of the 32-wide slice.
+  // MFMA operands: lane (g, n) reads row n of a 32-row block, chunk 2 s + g of
+  // the slice's half s.
   const int g = lane >> 5, n = lane & 31;
-  const int wv = w & 1, wr = w >> 1;
+  const int wv = w >> 1, wr = w & 1;
   int off[2];
 #pragma unroll
   for (int s = 0; s < 2; ++s) off[s] = n * kLmKT + (((2 * s + g) ^ ((n >> 2) & 3)) * 8);
-  f32x16_t acc[4][2];
+  f32x16_t acc[2][M];
 #pragma unroll
-  for (int vb = 0; vb < 4; ++vb)
+  for (int vb = 0; vb < 2; ++vb)
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int rb = 0; rb < M; ++rb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[vb][rb][r] = 0.0f;
+  bf16x8_t F[2][2 + M];                                  // per half: two W fragments, M H fragments
+  auto read = [&](const uint16_t* st, int s, int i) {
+    const uint16_t* p = i < 2 ? st + (64 * wv + 32 * i) * kLmKT : st + kTile + (32 * M * wr + 32 * (i - 2)) * kLmKT;
+    F[s][i] = *reinterpret_cast<const bf16x8_t*>(p + off[s]);
+  };
 
   const int nk = a.d / kLmKT;
-#pragma unroll
-  for (int t = 0; t < kLmNS - 1; ++t)
-    if (t < nk) issue(t);
-  for (int t = 0; t < nk; ++t) {
-    // stage t landed once only the (at most two) later stages' four blocks each remain
-    const int ahead = min(nk - 1 - t, kLmNS - 2);
-    if (ahead >= 2)
-      wait_vm_c<8>();
-    else if (ahead == 1)
-      wait_vm_c<4>();
-    else
-      wait_vm_c<0>();
-    // after the barrier every wave is done with stage t - 1, whose slot is
-    // refilled: one DMA block after every four MFMAs
-    __syncthreads();
-    const bool refill = t + kLmNS - 1 < nk;
-    const uint16_t* st = ring + (t % kLmNS) * kStage;
-    const uint16_t* at = st + (128 * wv) * kLmKT;
-    const uint16_t* bt = st + kTile + (64 * wr) * kLmKT;
-    bf16x8_t A[2][4], B[2][2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-#pragma unroll
-      for (int vb = 0; vb < 4; ++vb) A[s][vb] = *reinterpret_cast<const bf16x8_t*>(at + 32 * vb * kLmKT + off[s]);
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb) B[s][rb] = *reinterpret_cast<const bf16x8_t*>(bt + 32 * rb * kLmKT + off[s]);
-    }
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int vb = 0; vb < 4; ++vb) {
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-          acc[vb][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[s][vb], B[s][rb], acc[vb][rb], 0, 0, 0);
-        if (vb & 1) {
-          __builtin_amdgcn_sched_barrier(0);
-          if (refill) issue1(t + kLmNS - 1, 2 * s + (vb >> 1));
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
+  for (int t = 0; t < min(NS, nk); ++t) {
+    issue_w(0);
+    issue_w(1);
+    issue_h(0);
+    issue_h(1);
+    issued();
   }
+  wait_ahead(min(NS, nk) - 1);
+  barrier();
+  const uint16_t* st = ring;
+#pragma unroll
+  for (int i = 0; i < 2 + M; ++i) read(st, 0, i);
+
+  // Half s of stage t: 2 M MFMAs on F[s]; beside them the reads of the next
+  // half into F[s ^ 1], then the transfers of stage t + NS.
+  auto half = [&](auto half_tag, auto refill_tag, const uint16_t* next) {
+    constexpr int s = decltype(half_tag)::value, refill = decltype(refill_tag)::value;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 2 * M; ++i) {
+      acc[i & 1][i >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F[s][i & 1], F[s][2 + (i >> 1)], acc[i & 1][i >> 1], 0, 0, 0);
+      if (i < 2 + M) read(next, s ^ 1, i);
+      if (i == 2 * M - 1) {
+#pragma unroll
+        for (int k = 2 * M; k < 2 + M; ++k) read(next, s ^ 1, k);      // M = 1: three reads, two MFMAs
+      }
+      if (refill && s == 1 && i >= 2 * M - 2) {
+        issue_w(i & 1);
+        issue_h(i & 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (refill && s == 1) issued();
+  };
+  auto stage = [&](int t, auto refill_tag) {
+    half(Const<0>{}, refill_tag, st);
+    // Stage t + 1 has landed once only later ones are in flight. Past the
+    // barrier every wave holds its last operands of stage t, so its slot is free.
+    wait_ahead(refill_tag.value ? NS - 2 : max(nk - 2 - t, 0));
+    barrier();
+    st = st + SLOT == ring + NS * SLOT ? ring : st + SLOT;
+    // after the last stage this reads a slot that nobody refills; the operands are not used
+    half(Const<1>{}, refill_tag, st);
+  };
+  int t = 0;
+  for (; t + NS < nk; ++t) stage(t, Const<1>{});
+  for (; t < nk; ++t) stage(t, Const<0>{});
 
   // Epilogue: lane (g, n) holds C^T[vocab v][row n] for
-  // v = v0 + 128 wv + 32 vb + 8 (r / 4) + 4 g + r % 4.
-  const int vbase = v0 + 128 * wv + 4 * g;
+  // v = v0 + 64 wv + 32 vb + 8 (r / 4) + 4 g + r % 4.
+  const int v0 = vt * kLmNT;
+  const int vbase = v0 + 64 * wv + 4 * g;
   if (v0 + kLmNT > a.V) {                      // ragged last vocabulary tile only
 #pragma unroll
-    for (int vb = 0; vb < 4; ++vb)
+    for (int vb = 0; vb < 2; ++vb)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
         if (vbase + 32 * vb + 8 * (r >> 2) + (r & 3) >= a.V) {
-          acc[vb][0][r] = -__builtin_inff();
-          acc[vb][1][r] = -__builtin_inff();
+#pragma unroll
+          for (int rb = 0; rb < M; ++rb) acc[vb][rb][r] = -__builtin_inff();
         }
   }
+  barrier();                                   // the ring is read no more
+  DecPartial* part = reinterpret_cast<DecPartial*>(ring);   // [4][64 M]: one per (wv, listed row of the tile)
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
+  for (int rb = 0; rb < M; ++rb) {
     float mx = -__builtin_inff();
     int am = INT_MAX;
 #pragma unroll
-    for (int vb = 0; vb < 4; ++vb)
+    for (int vb = 0; vb < 2; ++vb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float x = acc[vb][rb][r];
@@ -220,25 +241,69 @@ __global__ __launch_bounds__(512, 1) void k_lm_head(LmArgs a) {
       }
     const float mo = __shfl_xor(mx, 32, 64);
     const int ao = __shfl_xor(am, 32, 64);
-    const float M = fmaxf(mx, mo);
-    int A = mx == M ? am : INT_MAX;
-    if (mo == M) A = min(A, ao);
-    const float nm = M == -__builtin_inff() ? 0.0f : -M * kLog2e;   // a slice past V sums to 0
+    const float mm = fmaxf(mx, mo);
+    int A = mx == mm ? am : INT_MAX;
+    if (mo == mm) A = min(A, ao);
+    const float nm = mm == -__builtin_inff() ? 0.0f : -mm * kLog2e;   // a slice past V sums to 0
     float sum = 0.0f;
 #pragma unroll
-    for (int vb = 0; vb < 4; ++vb)
+    for (int vb = 0; vb < 2; ++vb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(fmaf(acc[vb][rb][r], kLog2e, nm));
     sum += __shfl_xor(sum, 32, 64);
-    const int slot = r0 + 64 * wr + 32 * rb + n;
-    if (g == 0 && slot < count) {
+    if (g == 0) {
       DecPartial p;
-      p.m = M;
+      p.m = mm;
       p.s = sum;
       p.a = A;
       p.pad = 0;
-      a.slices[(int64_t)slot * a.parts + 2 * vt + wv] = p;
+      part[wv * 64 * M + 32 * M * wr + 32 * rb + n] = p;
     }
+  }
+  barrier();
+  // one thread per (listed row, 128-entry slice) joins the slice's two halves
+  const int x = threadIdx.x >> 1, h = threadIdx.x & 1;
+  if (x < 64 * M && r0 + x < count) {
+    const DecPartial p0 = part[2 * h * 64 * M + x], p1 = part[(2 * h + 1) * 64 * M + x];
+    DecPartial p;
+    p.m = fmaxf(p0.m, p1.m);
+    p.s = p.m == -__builtin_inff() ? p0.s + p1.s
+                                   : p0.s * __builtin_amdgcn_exp2f((p0.m - p.m) * kLog2e) +
+                                         p1.s * __builtin_amdgcn_exp2f((p1.m - p.m) * kLog2e);
+    p.a = min(p0.m == p.m ? p0.a : INT_MAX, p1.m == p.m ? p1.a : INT_MAX);
+    p.pad = 0;
+    a.slices[(int64_t)(r0 + x) * a.parts + 2 * vt + h] = p;
+  }
+}
+
+__global__ __launch_bounds__(512, 1) void k_lm_head(LmArgs a) {
+  static_assert(kLmNT == 256 && kLmMT == 256 && kLmKT == 32, "tiling below assumes these");
+  __shared__ __align__(1024) uint16_t ring[kLdsBytes / 2];
+  const int count = *a.count;
+  if (count == 0) return;
+  const int nvt = (a.V + kLmNT - 1) / kLmNT;
+  // The listed rows fall into units of 64, dealt evenly to the fewest row
+  // tiles of at most four units: 1035 rows are tiles of 4, 4, 3, 3 and 3 units
+  // (1088 rows) rather than five of 256 (1280), 125 rows one of 128. Whole
+  // calls before and after, by rows: LLaDA-8B head 12: 276 -> 197 us, 125: 277
+  // -> 220, 268: 517 -> 368, 502: 554 -> 493; Dream-7B head 1035: 1673 -> 1071.
+  const int units = (count + 63) / 64;
+  const int nact = (units + 3) / 4, base = units / nact, extra = units - base * nact;
+  // Workgroups b = x + 8 q run on XCD x. Consecutive q on one XCD take all row
+  // tiles of one vocabulary tile, which then share that XCD's L2 copy of the W
+  // slab (W is read about once; the hidden rows come from L2 or the Infinity
+  // Cache), and the XCDs take the vocabulary tiles in turn. One row tile per
+  // XCD took 403 us on 268 rows (two row tiles), a contiguous range of
+  // vocabulary tiles per XCD 230 us on 125 rows.
+  const int x = (int)(blockIdx.x & 7), q = (int)(blockIdx.x >> 3);
+  const int vt = (q / nact) * 8 + x, rt = q % nact;
+  if (vt >= nvt) return;
+  const int r0 = 64 * (rt * base + min(rt, extra));
+  switch (base + (rt < extra ? 1 : 0)) {
+    case 1: lm_tile<1>(a, ring, vt, r0, count); break;
+    case 2: lm_tile<2>(a, ring, vt, r0, count); break;
+    case 3: lm_tile<3>(a, ring, vt, r0, count); break;
+    default: lm_tile<4>(a, ring, vt, r0, count); break;
   }
 }
 
@@ -317,10 +382,7 @@ hipError_t launch_lm_rows(const LmArgs& a, hipStream_t s) {
 hipError_t launch_lm_gemm(const LmArgs& a, hipStream_t s) {
   const int nvt = (a.V + kLmNT - 1) / kLmNT;
   const int nrt = (a.n * a.L + kLmMT - 1) / kLmMT;
-  // enough workgroups per XCD for either order: nvt covers the one-row-tile
-  // order (an XCD serves at most nvt vocabulary tiles), the other needs
-  // ceil(nvt * nrt / 8)
-  const int per_xcd = max((nvt * nrt + 7) / 8, nvt);
+  const int per_xcd = (nvt + 7) / 8 * nrt;     // the row count is known on the device only
   hipLaunchKernelGGL(k_lm_head, dim3((unsigned)(8 * per_xcd)), dim3(512), 0, s, a);
   return hipGetLastError();
 }

@@ -119,10 +119,32 @@ def test_lm_head_medium(ctx, V, d):
 
 @pytest.mark.parametrize("n", [22, 60, 90])
 def test_lm_head_row_tile_orders(ctx, n):
-    # 2, 4 and 6 row tiles of 256 masked rows: the one-row-tile-per-XCD order
-    # and the order that keeps all row tiles of a vocabulary tile together
+    # 2, 4 and 6 row tiles, which share a vocabulary tile's slab on one XCD
     w = synth.custom(32, 2, 2, 16, 777, "bf16", [5 + 3 * i for i in range(n)], [64] * n, [i % 2 for i in range(n)])
     _, _, stats, _ = lm_case(ctx, w, 64, f"n={n} rows")
+    assert band_ok(stats), stats
+
+
+@pytest.mark.parametrize("d", [96, 288, 352])
+@pytest.mark.parametrize("rows", [1, 64, 65, 128, 129, 192, 193, 256, 257, 577])
+def test_lm_head_row_tile_sizes(ctx, rows, d):
+    # exact numbers of masked rows around the 64-row units that the row tiles
+    # are made of; 3, 9 and 11 K slices are fewer than, about and more than the
+    # 5 to 8 stages of the ring
+    n, L, V = 20, 32, 520
+    w = synth.custom(L, 2, 2, 16, V, "bf16", [3 + i for i in range(n)], [L] * n, [0] * n)
+    wv = synth.gen_lm_weight(w, d)
+    hidden = synth.gen_lm_hidden(w, wv)
+    rng = np.random.default_rng(rows * 1000 + d)
+    msk_c = np.zeros(n * L, np.uint8)
+    msk_c[rng.choice(n * L, size=rows, replace=False)] = 1
+    msk_c = msk_c.reshape(n, L)
+    tok_c = np.full((n, L), 5, np.int32)
+    got = run_lm(ctx, w, hidden, wv, tok_c, msk_c)
+    ref = oracle.lm_head_decode(w.reqs, L, hidden, wv, tok_c, msk_c, tau=w.tau, q_min=w.q_min, eos_id=w.eos_id,
+                                dtype="bf16", only=list(range(n)))
+    stats = check_decode(w, got, ref, reqs=w.reqs, label=f"rows={rows} d={d}", conf_tol=LM_CONF_TOL,
+                         alt_ids=near_ties(w, hidden, wv, msk_c, list(range(n))), tok_in=tok_c, msk_in=msk_c)
     assert band_ok(stats), stats
 
 
