@@ -18,7 +18,7 @@
 //             block: the epilogue reduces 32 logits per lane and row, exchanges
 //             once with the other half-wave and once through LDS. One DecPartial per (row,
 //             128-entry vocabulary slice).
-// k_lm_merge  one wave per listed row merges its slices into the DecPartial
+// k_lm_merge  one workgroup per listed row merges its slices into the DecPartial
 //             the selection reads.
 #include <float.h>
 #include <limits.h>
@@ -33,31 +33,47 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr float kLog2e = 1.4426950408889634f;
 
-__device__ inline bool listed(const LmArgs& a, int x) {
-  const int i = x / a.L, j = x - i * a.L;
-  const Geo q = geo_of(a.reqs[i], a.L);
-  return j < q.B && a.masked[x] != 0;
-}
-
+// Latency-bound (one workgroup): the flags of 4096 positions are loaded
+// at once and counted by ballots, so that a batch of up to 4096 positions waits
+// for one round trip to memory and two barriers: 256 positions 5.2 -> LMROWS8,
+// 2048 positions 5.1 -> LMROWS64 (a serial count and a scan of 1024 threads by
+// doubling, before).
 __global__ __launch_bounds__(1024) void k_lm_rows(LmArgs a) {
-  __shared__ int sc[1024];
-  const int total = a.n * a.L, t = threadIdx.x;
-  const int per = (total + 1023) / 1024;
-  const int x0 = min(t * per, total), x1 = min(x0 + per, total);
-  int c = 0;
-  for (int x = x0; x < x1; ++x) c += listed(a, x) ? 1 : 0;
-  sc[t] = c;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {      // inclusive scan of the per-thread counts
-    const int v = t >= o ? sc[t - o] : 0;
+  constexpr int NC = 4;                     // chunks of 1024 positions per trip
+  __shared__ int cnt[2][NC * 16];           // listed positions of (chunk, wave), by trip parity
+  const int total = a.n * a.L, t = threadIdx.x, w = t >> 6, lane = t & 63;
+  int pos = 0, trip = 0;
+  for (int x0 = 0; x0 < total; x0 += NC * 1024, trip ^= 1) {
+    bool on[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int x = min(x0 + c * 1024 + t, total - 1);
+      const int i = x / a.L, j = x - i * a.L;
+      const bs_req_desc r = a.reqs[i];
+      const uint8_t m = a.masked[x];
+      on[c] = x0 + c * 1024 + t < total && j < geo_of(r, a.L).B && m != 0;
+    }
+    unsigned long long bits[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      bits[c] = __ballot(on[c]);
+      if (lane == 0) cnt[trip][c * 16 + w] = __popcll(bits[c]);
+    }
     __syncthreads();
-    sc[t] += v;
-    __syncthreads();
+    int sum = cnt[trip][lane];              // NC * 16 == 64: inclusive scan over (chunk, wave)
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(sum, o, 64);
+      if (lane >= o) sum += v;
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int before = __shfl(sum, max(c * 16 + w - 1, 0), 64);
+      if (on[c]) a.rows[pos + (c * 16 + w ? before : 0) + __popcll(bits[c] & ((1ull << lane) - 1))] = x0 + c * 1024 + t;
+    }
+    pos += __shfl(sum, 63, 64);
   }
-  int pos = sc[t] - c;
-  for (int x = x0; x < x1; ++x)
-    if (listed(a, x)) a.rows[pos++] = x;
-  if (t == 1023) *a.count = sc[1023];
+  if (t == 0) *a.count = pos;
 }
 
 // LDS rows hold 32 bf16 of K (64 bytes, four 16-byte chunks). Chunk c of tile
@@ -323,27 +339,54 @@ __device__ inline int wave_min_i(int v) {
   return v;
 }
 
-__global__ __launch_bounds__(64) void k_lm_merge(LmArgs a) {
-  const int x = blockIdx.x, lane = threadIdx.x;
+// One workgroup per listed row. Latency-bound: a thread's parts (five of the
+// 1188 of a Dream-7B head) are loaded at once and kept, so that a row waits for
+// one round trip to memory: 125 rows x 988 parts 12.4 -> 5.4 us, 1035 rows x
+// 1188 parts 17.3 -> 7.2 us (one wave per row, two passes, before).
+__global__ __launch_bounds__(256) void k_lm_merge(LmArgs a) {
+  constexpr int NP = 8;
+  const int x = blockIdx.x, t = threadIdx.x, w = t >> 6;
   if (x >= *a.count) return;
   const DecPartial* p = a.slices + (int64_t)x * a.parts;
+  DecPartial q[NP];
+#pragma unroll
+  for (int k = 0; k < NP; ++k) {
+    if (t + 256 * k < a.parts)
+      q[k] = p[t + 256 * k];
+    else
+      q[k] = DecPartial{-__builtin_inff(), 0.0f, INT_MAX, 0};
+  }
   float M = -__builtin_inff();
-  for (int k = lane; k < a.parts; k += 64) M = fmaxf(M, p[k].m);
+#pragma unroll
+  for (int k = 0; k < NP; ++k) M = fmaxf(M, q[k].m);
+  for (int k = t + 256 * NP; k < a.parts; k += 256) M = fmaxf(M, p[k].m);
+  __shared__ float sm[4], ss[4];
+  __shared__ int sa[4];
   M = wave_max(M);
+  if ((t & 63) == 0) sm[w] = M;
+  __syncthreads();
+  M = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
   float S = 0.0f;
   int A = INT_MAX;
-  for (int k = lane; k < a.parts; k += 64) {
-    const DecPartial q = p[k];
-    if (q.m != -__builtin_inff()) S += q.s * __builtin_amdgcn_exp2f((q.m - M) * kLog2e);
-    if (q.m == M) A = min(A, q.a);
-  }
+  auto fold = [&](const DecPartial& v) {
+    if (v.m != -__builtin_inff()) S += v.s * __builtin_amdgcn_exp2f((v.m - M) * kLog2e);
+    if (v.m == M) A = min(A, v.a);
+  };
+#pragma unroll
+  for (int k = 0; k < NP; ++k) fold(q[k]);
+  for (int k = t + 256 * NP; k < a.parts; k += 256) fold(p[k]);
   S = wave_sum(S);
   A = wave_min_i(A);
-  if (lane == 0) {
+  if ((t & 63) == 0) {
+    ss[w] = S;
+    sa[w] = A;
+  }
+  __syncthreads();
+  if (t == 0) {
     DecPartial r;
     r.m = M;
-    r.s = S;
-    r.a = A;
+    r.s = (ss[0] + ss[1]) + (ss[2] + ss[3]);
+    r.a = min(min(sa[0], sa[1]), min(sa[2], sa[3]));
     r.pad = 0;
     a.row_part[a.rows[x]] = r;
   }
@@ -388,7 +431,7 @@ hipError_t launch_lm_gemm(const LmArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_lm_merge(const LmArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_lm_merge, dim3((unsigned)(a.n * a.L)), dim3(64), 0, s, a);
+  hipLaunchKernelGGL(k_lm_merge, dim3((unsigned)(a.n * a.L)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
