@@ -35,9 +35,9 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 // Latency-bound (one workgroup): the flags of 4096 positions are loaded
 // at once and counted by ballots, so that a batch of up to 4096 positions waits
-// for one round trip to memory and two barriers: 256 positions 5.2 -> LMROWS8,
-// 2048 positions 5.1 -> LMROWS64 (a serial count and a scan of 1024 threads by
-// doubling, before).
+// for one round trip to memory and one barrier: shortest launches of 256
+// positions 4.3 -> 3.1 us, of 2048 positions 4.9 -> 3.8 us (a serial count and a
+// scan of 1024 threads by doubling, before).
 __global__ __launch_bounds__(1024) void k_lm_rows(LmArgs a) {
   constexpr int NC = 4;                     // chunks of 1024 positions per trip
   __shared__ int cnt[2][NC * 16];           // listed positions of (chunk, wave), by trip parity
