@@ -418,7 +418,8 @@ int bs_mixed_state_step_noalloc(bs_ctx* ctx, const bs_req_desc* reqs, int n, int
  * bs_profile_begin arms a ring of max_steps calls: each following call of
  * these entry points records BS_PROFILE_PHASES + 1 HIP events on its stream,
  * until max_steps calls are recorded. For bs_mixed_state_step the phases are
- * attention over all layers, decode row reductions, selection; for
+ * attention over all layers, decode row reductions (with the merge of the last
+ * layer's split rows), selection; for
  * bs_lm_head_decode they are the masked-row list, the output-head GEMM with
  * its on-the-fly reduction, and the merge plus selection; for
  * bs_dual_cache_refresh the rotated-key and value scatter, the attention,

@@ -97,7 +97,8 @@ struct AttnArgs {
 constexpr int kMhaWaves = 4;  // waves (independent items) per workgroup of the single-wave bf16 kernel
 
 hipError_t launch_attn_f32(const AttnArgs& a, int n_req, hipStream_t s);
-hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s);
+// merge = false leaves the merge of split rows to the caller (launch_decode_rows)
+hipError_t launch_attn_bf16(const AttnArgs& a, bool merge, hipStream_t s);
 
 // ---------------------------------------------------------------- decode
 struct DecPartial {
@@ -153,14 +154,16 @@ hipError_t launch_decode(const DecArgs& a, bs_dtype dt, hipStream_t s);
 
 // launch_decode with mark(2) after the row reductions and mark(3) after the
 // selection (the step's phase-timing event indices); mark returns a hipError_t.
+// `merge`: NULL, or the attention whose split rows the row reductions' launch
+// merges beside its own work (launched with merge = false).
 template <class Mark>
-hipError_t launch_decode_marked(const DecArgs& a, bs_dtype dt, hipStream_t s, Mark mark);
-hipError_t launch_decode_rows(const DecArgs& a, bs_dtype dt, hipStream_t s);
+hipError_t launch_decode_marked(const DecArgs& a, bs_dtype dt, const AttnArgs* merge, hipStream_t s, Mark mark);
+hipError_t launch_decode_rows(const DecArgs& a, bs_dtype dt, const AttnArgs* merge, hipStream_t s);
 hipError_t launch_decode_select(const DecArgs& a, hipStream_t s);
 
 template <class Mark>
-hipError_t launch_decode_marked(const DecArgs& a, bs_dtype dt, hipStream_t s, Mark mark) {
-  hipError_t e = launch_decode_rows(a, dt, s);
+hipError_t launch_decode_marked(const DecArgs& a, bs_dtype dt, const AttnArgs* merge, hipStream_t s, Mark mark) {
+  hipError_t e = launch_decode_rows(a, dt, merge, s);
   if (e == hipSuccess) e = mark(2);
   if (e == hipSuccess) e = launch_decode_select(a, s);
   if (e == hipSuccess) e = mark(3);

@@ -973,7 +973,7 @@ int bs_dual_cache_block_attention(bs_ctx* c, const bs_req_desc* reqs, int n, int
   if (st) return st;
   AttnArgs a = attention_args(sl->d, sl->meta, L, Hq, Hkv, D, R, W, scale, write_back, ws);
   a.q = q; a.k_new = k_new; a.v_new = v_new; a.k_cache = k_cache; a.v_cache = v_cache; a.out = out;
-  hipError_t e = dt == BS_F32 ? launch_attn_f32(a, n, s) : launch_attn_bf16(a, s);
+  hipError_t e = dt == BS_F32 ? launch_attn_f32(a, n, s) : launch_attn_bf16(a, true, s);
   return finish(c, sl, s, e, "attention launch");
 }
 
@@ -1223,7 +1223,8 @@ static hipError_t step_launch(bs_ctx* c, const void* dblob, const int* meta, int
     a.q = q[l]; a.k_new = k_new[l]; a.v_new = v_new[l]; a.k_cache = k_cache[l]; a.v_cache = v_cache[l]; a.out = out[l];
     a.mask_words = use_words && l == 0 ? words : nullptr;
     a.masked = masked; a.msk_rs = masked_row_stride;
-    e = dt == BS_F32 ? launch_attn_f32(a, n, s) : launch_attn_bf16(a, s);
+    // the last layer's split rows are merged by the row reductions' launch
+    e = dt == BS_F32 ? launch_attn_f32(a, n, s) : launch_attn_bf16(a, l + 1 < n_layers, s);
   }
   if (e == hipSuccess) e = prof_mark(c, 1, s);
   if (e == hipSuccess) {
@@ -1233,7 +1234,8 @@ static hipError_t step_launch(bs_ctx* c, const void* dblob, const int* meta, int
     d.dense = 1; d.tok_rs = tokens_row_stride; d.msk_rs = masked_row_stride;
     d.pos_out = pos_out;
     d.words = use_words ? words : nullptr;
-    e = launch_decode_marked(d, logits_dt, s, [&](int ph) { return prof_mark(c, ph, s); });
+    const AttnArgs* merge = n_layers > 0 && a.n_merge > 0 ? &a : nullptr;
+    e = launch_decode_marked(d, logits_dt, merge, s, [&](int ph) { return prof_mark(c, ph, s); });
   }
   if (e == hipSuccess && c->prof.on && c->prof.used < c->prof.cap) ++c->prof.used;
   return e;

@@ -110,7 +110,9 @@ __device__ inline void wait_stages(int k) {
 // scheduling fences: one MFMA, then one LDS read or one transfer.
 // Measured on a Dream-7B head (V = 152064, d = 3584), 1035 listed rows: 1065 us,
 // MFMA busy 60% at 1.75 GHz. With a barrier before the reads of a whole slice
-// and five 256-row tiles the same rows took 1640 us.
+// and five 256-row tiles the same rows took 1640 us. Four waves of 128 x 32 M
+// (two thirds of the LDS reads, accumulators in AGPRs, one wave per SIMD) took
+// 12% longer than eight.
 template <int M>
 __device__ inline void lm_tile(const LmArgs& a, uint16_t* ring, int vt, int r0, int count) {
   constexpr int HB = 4 * M;                              // 1 KiB blocks (16 rows) of the H tile

@@ -178,6 +178,25 @@ def test_fused_step_split_kv_stragglers(ctx, Hq, Hkv):
         check_attention(w, la["out"], oracle.widen(lc["out"], w.dtype), label="split vs whole rows")
 
 
+@pytest.mark.parametrize("L,Hq,Hkv,D", [(32, 4, 4, 64), (32, 4, 4, 128), (64, 14, 2, 64), (48, 14, 2, 128)])
+def test_fused_step_split_rows_in_each_layer(ctx, L, Hq, Hkv, D):
+    # split rows of the first layer are merged by a launch of their own, those
+    # of the last by the row reductions' launch; a row of 9 pieces or more
+    # takes two batches of loads
+    torch, bs, bstep = lazy()
+    w = synth.custom(L, Hq, Hkv, D, 1024, "bf16", [5000, 40, 700], [2 * L, 3 * L, L + 3], [1, 0, 1], layers=2,
+                     kv_sigma=1 / D ** 0.5)
+    st, host = make_state(w)
+    items, nparts = bs.bs_attention_work_list(w.reqs, L, Hq, Hkv, D, bs.BS_BF16, True)
+    assert nparts > 8
+    bstep.run_step(ctx, st, w.reqs, want_conf=True)
+    torch.cuda.synchronize()
+    got = snapshot(st)
+    ref = oracle.mixed_state_step(w.reqs, w.L, host["tokens"], host["mask"], host["layers"], host["logits"],
+                                  tau=w.tau, q_min=w.q_min, eos_id=w.eos_id, dtype=w.dtype)
+    check_step(w, got, ref, host, f"split L={L} D={D}")
+
+
 def test_fused_step_equals_separate_calls(ctx):
     """Same kernels, same order: the fused call and the K1/K2/K3/K1^-1
     sequence give identical bytes (GQA shapes, three layers)."""
