@@ -92,6 +92,7 @@ struct AttnArgs {
   float* parts;
   const AttnMerge* merges;
   int n_merge;
+  int pair;   // the items run two workgroups to a CU (where the kernel has that form)
 };
 
 constexpr int kMhaWaves = 4;  // waves (independent items) per workgroup of the single-wave bf16 kernel

@@ -40,7 +40,7 @@ struct Slot {
   size_t cap = 0;
   std::vector<unsigned char> key;
   uint64_t hash = 0;
-  int meta[6] = {0, 0, 0, 0, 0, 0};  // blob layout (offsets, counts) recorded at build time
+  int meta[7] = {0, 0, 0, 0, 0, 0, 0};  // blob layout (offsets, counts) recorded at build time
   hipEvent_t ready = nullptr;  // recorded after the upload
   hipEvent_t done = nullptr;   // recorded after the last launch that read it
   hipStream_t stream = nullptr;
@@ -154,7 +154,7 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 // Blob = descriptors followed by an optional work list, 16-byte aligned parts.
 struct Blob {
   std::vector<unsigned char> bytes;
-  int meta[6] = {0, 0, 0, 0, 0, 0};
+  int meta[7] = {0, 0, 0, 0, 0, 0, 0};
   size_t add(const void* p, size_t n) {
     size_t off = (bytes.size() + 15) & ~size_t(15);
     bytes.resize(off + n);
@@ -508,13 +508,35 @@ int split_items(const std::vector<AttnItem>& items, int cap, std::vector<AttnIte
   return parts;
 }
 
+// Whether a list's items run two workgroups to a CU (k_attn_bf16_pair: groups
+// of up to four waves at D = 128) instead of one. Two hide each other's first
+// and last tiles, but each then runs slower, so a list whose longest item lasts
+// as long as the launch does not gain. In tiles, with kPieceOverhead per item:
+// paired when a CU's share of the list is at least 1.05 times the longest item.
+// Measured on both sides, by that quotient (one per CU -> two, us): LLaDA-8B
+// heads with L = 64, 3.1: 81.3 -> 66.7, 2.15: 136 -> 129, 1.54: 42 -> 35, 1.19:
+// 39.4 -> 31.7; 1.00: 68.5 -> 70.9 and 144.5 -> 153.0, 0.81: 51.3 -> 54.4. Two,
+// three and four query heads per KV head, 3.3: 142 -> 131 and 148 -> 136, 2.2:
+// 91 -> 88.7, 95.8 -> 92.6 and 101 -> 97, 1.09: 54.3 -> 51.2 and 56.8 -> 51.0.
+// The pieces of a list that split_cap cut are about as long as a CU's share.
+// The kernels' results are the same bit for bit.
+bool pair_workgroups(const AttnItem* items, size_t N) {
+  int64_t total = 0;
+  int longest = 0;
+  for (size_t i = 0; i < N; ++i) {
+    total += items[i].t1 - items[i].t0;
+    longest = std::max(longest, items[i].t1 - items[i].t0);
+  }
+  return (double)total + kPieceOverhead * (double)N >= 1.05 * kPlanCUs * (longest + kPieceOverhead);
+}
+
 // Partial-slot bytes of a plan with `parts` slots.
 size_t part_bytes(int parts, int L, int Hq, int Hkv, int D) {
   return (size_t)parts * waves_per_item(L, Hq, Hkv) * part_wave_floats(D) * sizeof(float);
 }
 
 // Descriptors, then (bf16) the work items above, then (split) the merge list;
-// meta = {descriptors, items, item count, merges, merge count, partial slots}.
+// meta = {descriptors, items, item count, merges, merge count, partial slots, pair_workgroups}.
 void attention_blob(Blob& blob, const bs_req_desc* reqs, int n, int L, int Hq, int Hkv, bs_dtype dt, bool split) {
   blob.meta[0] = (int)blob.add(reqs, sizeof(bs_req_desc) * n);
   if (dt == BS_BF16) {
@@ -540,6 +562,7 @@ void attention_blob(Blob& blob, const bs_req_desc* reqs, int n, int L, int Hq, i
     blob.meta[3] = (int)blob.add(merges.data(), sizeof(AttnMerge) * merges.size());
     blob.meta[4] = (int)merges.size();
     blob.meta[5] = parts;
+    blob.meta[6] = pair_workgroups(list.data(), list.size()) ? 1 : 0;
   }
 }
 
@@ -554,6 +577,7 @@ AttnArgs attention_args(const void* dblob, const int* meta, int L, int Hq, int H
   a.n_items = meta[2];
   a.merges = reinterpret_cast<const AttnMerge*>(base + meta[3]);
   a.n_merge = meta[4];
+  a.pair = meta[6];
   a.parts = static_cast<float*>(parts);
   a.L = L; a.Hq = Hq; a.Hkv = Hkv; a.D = D; a.G = Hq / Hkv; a.RB = (L + 31) / 32; a.R = R; a.W = W;
   a.RBW = a.G * a.RB > 8 ? 1 : a.RB;
@@ -1327,7 +1351,8 @@ int bs_mixed_state_step_noalloc(bs_ctx* c, const bs_req_desc* reqs, int n, int L
   unsigned char* h = static_cast<unsigned char*>(sp.stage[k]);
   std::memcpy(h, reqs, sizeof(bs_req_desc) * n);
   if (n_items) attention_items_into(reinterpret_cast<AttnItem*>(h + items_off), sp.tmp.get(), reqs, n, L, Hq, Hkv);
-  const int meta[6] = {0, (int)items_off, (int)n_items, 0, 0, 0};   // whole rows: no merge list
+  const int pair = n_items && pair_workgroups(reinterpret_cast<const AttnItem*>(h + items_off), n_items) ? 1 : 0;
+  const int meta[7] = {0, (int)items_off, (int)n_items, 0, 0, 0, pair};   // whole rows: no merge list
   hipError_t e = hipMemcpyAsync(dscratch, h, blob_bytes, hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return hip_fail(c, e, "hipMemcpyAsync(scratch)");
   e = hipEventRecord(sp.copied[k], s);

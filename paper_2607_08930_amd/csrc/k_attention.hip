@@ -444,10 +444,14 @@ __device__ inline int swz(int row) {
   return ((row & 3) << 1) | ((row >> 2) & 1);
 }
 
-// compile-time flag passed to a generic lambda
+// compile-time flag or number passed to a generic lambda
 template <bool B>
 struct Flag {
   static constexpr bool value = B;
+};
+template <int N>
+struct Num {
+  static constexpr int value = N;
 };
 
 // One (request, KV head) item processed by GW waves that share its K/V tiles:
@@ -467,7 +471,12 @@ struct Flag {
 // so fields read through a reference would be loaded again after every issue,
 // as vector loads whose waits also drain the DMA in flight (measured: 2.6 us
 // of the skewed Dream-7B batch's attention).
-template <int D, int KT, int NS, bool SHARED, int NI, int I0>
+//
+// PAIR (group loop): five slots of one tensor each, three of K and two of V,
+// instead of NS stages of both, so that two workgroups fit a CU's LDS at
+// D = 128. K runs two tiles ahead and V one; the arithmetic and its order are
+// the same.
+template <int D, int KT, int NS, bool SHARED, int NI, int I0, bool PAIR = false>
 __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t* ring, int GW, int wg,
                                  int lane) {
   constexpr int NKK = D / 16;
@@ -503,13 +512,16 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
   const uint32_t ring_lds = lds_addr(ring) + (uint32_t)(u * RPB * D * 2);
   auto row_of = [&](int r) { return r * NI * RPB + urow; };
   auto chunk_of = [&](int row) { return dslot ^ swz<NCH>(row); };
-  auto issue = [&](int stage, int tb) {
-    const uint32_t sbase = __builtin_amdgcn_readfirstlane(ring_lds + (uint32_t)(stage * STAGE * 2));
+  // blocks k0 .. k1 - 1 of this wave's share of the tile at key tb; K goes to
+  // element offset `dst` of the ring, V one tile further
+  auto issue_blocks = [&](int dst, int tb, auto k0_tag, auto k1_tag) {
+    constexpr int K0 = decltype(k0_tag)::value, K1 = decltype(k1_tag)::value;
+    const uint32_t sbase = __builtin_amdgcn_readfirstlane(ring_lds + (uint32_t)(dst * 2));
     if (tb + KT <= len && (tb + KT <= bs || tb >= be)) {
       // whole tile inside the cached part of the row: uniform base + lane offset
       const uint64_t kb = uniform64(kcb + (int64_t)tb * D), vb = uniform64(vcb + (int64_t)tb * D);
 #pragma unroll
-      for (int k = 0; k < PB; ++k) {
+      for (int k = K0; k < K1; ++k) {
         const int tensor = k / RPI, r = k % RPI;
         const int row = row_of(r);
         dma16_sv_once(sbase + (uint32_t)((tensor * TILE + r * NI * RPB * D) * 2), tensor ? vb : kb,
@@ -518,7 +530,7 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
     } else {
       // tile holds fresh block rows or runs past the row end: per-lane sources
 #pragma unroll
-      for (int k = 0; k < PB; ++k) {
+      for (int k = K0; k < K1; ++k) {
         const int tensor = k / RPI, r = k % RPI;
         const int row = row_of(r);
         const int t = min(tb + row, len - 1);        // rows past the end repeat a valid key (masked later)
@@ -529,6 +541,10 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
       }
     }
   };
+  auto issue = [&](int stage, int tb) { issue_blocks(stage * STAGE, tb, Num<0>{}, Num<PB>{}); };
+  // PAIR: one tensor of tile t of the item
+  auto issue_k = [&](int t, int tb) { issue_blocks(t % 3 * TILE, tb, Num<0>{}, Num<RPI>{}); };
+  auto issue_v = [&](int t, int tb) { issue_blocks((2 + t % 2) * TILE, tb, Num<RPI>{}, Num<PB>{}); };
   // issuing waves: wait until at most x (< NS) stages of this wave's DMA are
   // in flight (a count above the 6-bit vmcnt field waits for everything)
   auto wait_stages = [&](int x) {
@@ -557,9 +573,9 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
   const bool do_wb = a.write_back && it.rb == 0;
   uint16_t* kcw = static_cast<uint16_t*>(a.k_cache) + cache_off;
   uint16_t* vcw = static_cast<uint16_t*>(a.v_cache) + cache_off;
-  // chunk cid of the tile's fresh rows (K then V) by lane
-  // (wg - w0) * 64 + lane of the storing waves [w0, GW)
-  auto write_back_tile = [&](const uint16_t* st, int tb) {
+  // chunk cid of the tile's fresh rows (of K at kt, then of V at vt; either may
+  // be NULL) by lane (wg - w0) * 64 + lane of the storing waves [w0, GW)
+  auto write_back_tile = [&](const uint16_t* kt, const uint16_t* vt, int tb) {
     const int r0 = max(bs, tb) - tb, r1 = min(be, tb + KT) - tb;
     const int w0 = GW > NI ? NI : 0;
     if (!do_wb || r0 >= r1 || wg < w0) return;
@@ -567,7 +583,8 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
     const int gt = (wg - w0) * 64 + lane, gth = (GW - w0) * 64;
 #pragma unroll
     for (int tensor = 0; tensor < 2; ++tensor) {
-      const uint16_t* src = st + tensor * TILE;
+      const uint16_t* src = tensor ? vt : kt;
+      if (src == nullptr) continue;
       uint16_t* dst = tensor ? vcw : kcw;
       for (int cid = gt; cid < nc; cid += gth) {
         const int row = r0 + cid / NCH, c = cid % NCH;
@@ -594,7 +611,14 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
   }
   // prologue: stages 0 .. NS-2 (issued before anything else so the first
   // tiles are in flight while the queries load)
-  if (issuer) {
+  if constexpr (PAIR) {
+    if (issuer && ntiles > 0) {
+      issue_k(0, tb0);
+      issue_v(0, tb0);
+      if (ntiles > 1) issue_k(1, tb0 + KT);
+      if (ntiles > 2) issue_k(2, tb0 + 2 * KT);
+    }
+  } else if (issuer) {
 #pragma unroll
     for (int st = 0; st < NS - 1; ++st)
       if (st < ntiles) issue(st, tb0 + st * KT);
@@ -687,8 +711,22 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
       }
     };
 
+    auto kslot = [&](int t) -> const uint16_t* { return ring + (PAIR ? t % 3 * TILE : t % NS * STAGE); };
+    auto vslot = [&](int t) -> const uint16_t* { return ring + (PAIR ? (3 + t % 2) * TILE : t % NS * STAGE + TILE); };
+
     // tile 0 resident (the later prologue stages may still be in flight)
-    if (issuer) wait_stages(min(ntiles - 1, NS - 2));
+    if constexpr (PAIR) {
+      if (issuer) {
+        if (ntiles > 2)
+          wait_vm_c<3 * RPI>();
+        else if (ntiles > 1)
+          wait_vm_c<2 * RPI>();
+        else
+          wait_vm_c<RPI>();
+      }
+    } else if (issuer) {
+      wait_stages(min(ntiles - 1, NS - 2));
+    }
     __syncthreads();
 #pragma unroll
     for (int rr = 0; rr < 16; ++rr) {
@@ -702,7 +740,7 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
     auto body = [&](auto first_tag, int tile) {
       constexpr bool FIRST = decltype(first_tag)::value;
       const int tb = tb0 + tile * KT;
-      const uint16_t* vprev = ring + ((tile + NS - 1) % NS) * STAGE + TILE;
+      const uint16_t* vprev = vslot(FIRST ? 0 : tile - 1);
       mask_ragged(tb);
       // ---- block 1
       bf16x8_t vf[3];
@@ -763,9 +801,26 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
             for (int rr = 0; rr < 16; ++rr) o[dt][rr] *= alpha;
         }
       }
-      // ---- barrier: tile + 1 landed (stages up to tile + NS - 2 were
-      // issued); every wave is done with tile - 1, whose slot is refilled
-      if (tile + 1 < ntiles) {
+      if constexpr (PAIR) {
+        // ---- barrier: K of tile + 1 and V of tile landed (only K of tile + 2
+        // was issued after them); every wave is done with V of tile - 1 and K
+        // of tile (whose fresh rows are stored by now), whose slots are
+        // refilled
+        write_back_tile(kslot(tile), nullptr, tb);
+        if (issuer) {
+          if (tile + 2 < ntiles)
+            wait_vm_c<RPI>();
+          else
+            wait_vm_c<0>();
+        }
+        __syncthreads();
+        if (issuer) {
+          if (tile + 1 < ntiles) issue_v(tile + 1, tb + KT);
+          if (tile + 3 < ntiles) issue_k(tile + 3, tb + 3 * KT);
+        }
+      } else if (tile + 1 < ntiles) {
+        // ---- barrier: tile + 1 landed (stages up to tile + NS - 2 were
+        // issued); every wave is done with tile - 1, whose slot is refilled
         if (issuer) wait_stages(min(ntiles - 1, tile + NS - 2) - tile - 1);
         __syncthreads();
         const int nxt = tile + NS - 1;
@@ -773,7 +828,7 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
       }
       // ---- block 2 (on the last tile the scores read a resident slot and
       // are discarded)
-      const uint16_t* knext = ring + ((tile + 1) % NS) * STAGE;
+      const uint16_t* knext = kslot(tile + 1);
       bf16x8_t kf[3];
       kf[0] = kread(knext, 0);
       kf[1] = kread(knext, 1);
@@ -808,11 +863,11 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      write_back_tile(ring + (tile % NS) * STAGE, tb);
+      write_back_tile(PAIR ? nullptr : kslot(tile), vslot(tile), tb);
     };
     if (ntiles > 0) body(Flag<true>{}, 0);
     for (int tile = 1; tile < ntiles; ++tile) body(Flag<false>{}, tile);
-    pv_plain(ring + ((ntiles + NS - 1) % NS) * STAGE + TILE);
+    pv_plain(vslot(ntiles > 0 ? ntiles - 1 : NS - 1));
   } else {
     // The fresh block rows a tile holds are stored from the LDS tile after
     // the tile is consumed, always as SPT full store instructions per tensor
@@ -1013,6 +1068,16 @@ __global__ __launch_bounds__(512, 1) void k_attn_bf16_group(AttnArgs a) {
   attn_item<D, 64, NS, true, NI, 0>(a, a.items[blockIdx.x], lds, blockDim.x >> 6, w, threadIdx.x & 63);
 }
 
+// The same for groups of up to four waves, two workgroups to a CU: one's
+// prologue and epilogue pass under the other's loop (pair_workgroups says for
+// which lists).
+template <int D, int NI>
+__global__ __launch_bounds__(256, 2) void k_attn_bf16_pair(AttnArgs a) {
+  __shared__ __align__(1024) uint16_t lds[5 * 64 * D];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  attn_item<D, 64, 4, true, NI, 0, true>(a, a.items[blockIdx.x], lds, blockDim.x >> 6, w, threadIdx.x & 63);
+}
+
 // Split-KV merge as a launch of its own (merge_rows; launched at 256 threads).
 template <int D>
 __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
@@ -1024,6 +1089,8 @@ hipError_t launch_bf16_d(const AttnArgs& a, int GW, bool merge, hipStream_t s) {
   if (GW == 1) {
     constexpr int NS = 2, NW = kMhaWaves;
     hipLaunchKernelGGL((k_attn_bf16_wave<D, NS, NW>), dim3((a.n_items + NW - 1) / NW), dim3(64 * NW), 0, s, a);
+  } else if (D == 128 && GW <= 4 && a.pair) {   // at D = 64 the whole ring is half the LDS already
+    hipLaunchKernelGGL((k_attn_bf16_pair<D, 2>), dim3(a.n_items), dim3(64 * GW), 0, s, a);
   } else if (GW < 4) {
     hipLaunchKernelGGL((k_attn_bf16_group<D, 4, 2>), dim3(a.n_items), dim3(64 * GW), 0, s, a);
   } else {

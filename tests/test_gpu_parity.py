@@ -383,6 +383,30 @@ def test_attention_group_ring_phases(ctx, Hq, Hkv, D):
     _att(ctx, at_start, f"G{Hq // Hkv} D{D} block first")
 
 
+@pytest.mark.parametrize("L,Hq,Hkv", [(64, 64, 64), (48, 64, 64), (32, 96, 32), (16, 128, 32)])
+def test_attention_two_workgroups_per_cu(ctx, L, Hq, Hkv):
+    # a batch whose share per CU is well above its longest item runs the
+    # five-slot ring (three K tiles, two V tiles): rows of 1 to 7 tiles, whole
+    # and ragged, cover every position of the last tile in both rings, with the
+    # fresh block in the last tiles or the first; a request alone (one workgroup
+    # per CU) gives the same bits
+    lens = [1, 33, 64, 65, 128, 129, 192, 193, 255, 256, 257, 320, 383, 384, 447, 448]
+    at_end = synth.custom(L, Hq, Hkv, 128, 10, "bf16", [max(t - L, 0) for t in lens], [min(t, L) for t in lens],
+                          [0] * len(lens), kv_sigma=0.1, q_sigma=3.0)
+    at_start = synth.custom(L, Hq, Hkv, 128, 10, "bf16", [0] * len(lens), lens, [0] * len(lens), kv_sigma=0.1,
+                            q_sigma=3.0, variant=1)
+    for w in (at_end, at_start):
+        tiles = [Hkv * (-(-t // 64)) for t in lens]
+        assert sum(tiles) + 2 * Hkv * len(lens) >= 1.05 * 256 * (max(lens) // 64 + 2), "the list should be paired"
+        _att(ctx, w, f"L{L} G{Hq // Hkv}")
+    full, _, _, inp = run_attention(ctx, at_end, split=False)
+    for i in (0, 7, 15):
+        one, _, _, _ = run_attention(ctx, at_end, reqs=at_end.reqs[i:i + 1], q=inp["q"][i:i + 1],
+                                     kn=inp["k_new"][i:i + 1], vn=inp["v_new"][i:i + 1], kc=inp["k_cache"],
+                                     vc=inp["v_cache"], split=False)
+        assert np.array_equal(one[0], full[i]), f"request {i} alone differs from in-batch"
+
+
 @pytest.mark.parametrize("L,Hq,Hkv,D", [(8, 2, 2, 64), (5, 6, 2, 64), (24, 3, 3, 128), (9, 14, 2, 128),
                                         (64, 2, 1, 128), (16, 1, 1, 256), (33, 2, 2, 256)])
 def test_attention_fp32_matrix_tiles(ctx, L, Hq, Hkv, D):
