@@ -1088,9 +1088,17 @@ template <int D>
 hipError_t launch_bf16_d(const AttnArgs& a, int GW, bool merge, hipStream_t s) {
   if (GW == 1) {
     constexpr int NS = 2, NW = kMhaWaves;
-    hipLaunchKernelGGL((k_attn_bf16_wave<D, NS, NW>), dim3((a.n_items + NW - 1) / NW), dim3(64 * NW), 0, s, a);
+    // Up to 512 items a workgroup is one wave, so that they spread over all the
+    // CUs (four to a workgroup leave half the chip idle at 512): LLaDA-8B heads,
+    // 128 items 31.4 -> 27.1 us, 256: 31.8 -> 27.7, 512: 38.5 -> 35.0; at 768 and
+    // 1024 four to a workgroup, dealt by length, are the faster (46.1 against
+    // 46.7, 59.0 against 60.6). 64-key tiles for the lone waves: 27.6, 29.1, 38.1.
+    if (a.n_items <= 512)
+      hipLaunchKernelGGL((k_attn_bf16_wave<D, NS, 1>), dim3(a.n_items), dim3(64), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_attn_bf16_wave<D, NS, NW>), dim3((a.n_items + NW - 1) / NW), dim3(64 * NW), 0, s, a);
   } else if (D == 128 && GW <= 4 && a.pair) {   // at D = 64 the whole ring is half the LDS already
-    hipLaunchKernelGGL((k_attn_bf16_pair<D, 2>), dim3(a.n_items), dim3(64 * GW), 0, s, a);
+    hipLaunchKernelGGL((k_attn_bf16_pair<128, 2>), dim3(a.n_items), dim3(64 * GW), 0, s, a);
   } else if (GW < 4) {
     hipLaunchKernelGGL((k_attn_bf16_group<D, 4, 2>), dim3(a.n_items), dim3(64 * GW), 0, s, a);
   } else {
