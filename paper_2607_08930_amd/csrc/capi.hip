@@ -401,17 +401,26 @@ void attention_items_into(AttnItem* items, AttnItem* tmp, const bs_req_desc* req
 constexpr int kPlanCUs = 256;
 constexpr double kPieceOverhead = 2.0;
 constexpr double kMergeFixed = 3.0;        // the merge launch, in tiles
-constexpr double kMergePerPart = 0.02;     // per partial read back
+// The merge's cost per partial read back: a partial of the shared-tile kernel
+// holds up to eight waves' output, one of the single-wave kernel one wave's.
+// Measured on LLaDA-8B heads (us of attention and merge; 0.02 for both before):
+// 4 requests 27.3 whole -> 19.5 in 320 pieces, 3: 26.1 -> 17.0, 2: 16.8 -> 14.8, 1:
+// 14.9 -> 13.9 in pieces of 2 instead of 3 tiles. At 0.003, 12 requests were cut
+// into 672 items and took 35.1 instead of 30.0.
+constexpr double kMergePerPartShared = 0.02;
+constexpr double kMergePerPartWave = 0.01;
 
 struct PlanShape {
   int group;          // work items per workgroup (one workgroup per CU)
   double full_load;   // per-tile slowdown with every slot busy
+  double per_part;    // merge cost of a partial
 };
 
 bool shared_tile_path(int L, int Hq, int Hkv) { return !(Hq == Hkv && L <= 32); }
 
 PlanShape plan_shape(int L, int Hq, int Hkv) {
-  return shared_tile_path(L, Hq, Hkv) ? PlanShape{1, 1.3} : PlanShape{kMhaWaves, 2.0};
+  return shared_tile_path(L, Hq, Hkv) ? PlanShape{1, 1.3, kMergePerPartShared}
+                                      : PlanShape{kMhaWaves, 2.0, kMergePerPartWave};
 }
 
 int waves_per_item(int L, int Hq, int Hkv) {
@@ -467,7 +476,7 @@ int split_cap(const std::vector<int>& nt, const PlanShape& ps) {
       for (int r = t; r > 0; r -= cap) w.push_back(std::min(r, cap));
       parts += (t + cap - 1) / cap;
     }
-    const double est = launch_estimate(w, ps) + kMergeFixed + kMergePerPart * parts;
+    const double est = launch_estimate(w, ps) + kMergeFixed + ps.per_part * parts;
     if (est < best) {
       best = est;
       best_cap = cap;
