@@ -95,7 +95,20 @@ struct AttnArgs {
   int pair;   // the items run two workgroups to a CU (where the kernel has that form)
 };
 
-constexpr int kMhaWaves = 4;  // waves (independent items) per workgroup of the single-wave bf16 kernel
+// Waves (independent items) per workgroup of the single-wave bf16 kernel, whose
+// 256 CUs hold four each: four, dealt by length, for lists that the chip holds
+// at once; one for lists of at most kMhaSpread items, so that they spread over
+// the CUs; two, longest first, for lists longer than kMhaRound, where a CU takes
+// the next workgroup when one is done (four to a workgroup wait for the longest
+// of them). Measured on LLaDA-8B heads (us, four to a workgroup -> as here): 128
+// items 31.4 -> 27.1, 256: 31.8 -> 27.7, 512: 38.5 -> 35.0; 1152: 81.6 -> 68.8,
+// 1536: 94.4 -> 88.0, 2048: 113.4 -> 109.8, 3072: 171 -> 165. Between the lines
+// four are the faster: 640 items 41.1 (one 41.2, two 44.1), 768: 46.1 (46.7,
+// 48.5), 1024: 58.4 (60.6, 59.2). One to a workgroup above: 1152: 69.1, 1536:
+// 90.8, 3072: 169.9.
+constexpr int kMhaWaves = 4;
+constexpr int kMhaSpread = 512;
+constexpr int kMhaRound = 1024;
 
 hipError_t launch_attn_f32(const AttnArgs& a, int n_req, hipStream_t s);
 // merge = false leaves the merge of split rows to the caller (launch_decode_rows)

@@ -1044,8 +1044,8 @@ __device__ inline void attn_item(const AttnArgs& a, const AttnItem it, uint16_t*
 }
 
 // One query head per KV head and at most 32 block rows (MHA with L <= 32):
-// NW independent waves per workgroup, each owning one item and an NS-stage
-// ring of 32-key tiles.
+// NW independent waves per workgroup (see kMhaWaves), each owning one item and an
+// NS-stage ring of 32-key tiles.
 template <int D, int NS, int NW>
 __global__ __launch_bounds__(64 * NW, 1) void k_attn_bf16_wave(AttnArgs a) {
   constexpr int STAGE = 2 * 32 * D;
@@ -1053,8 +1053,14 @@ __global__ __launch_bounds__(64 * NW, 1) void k_attn_bf16_wave(AttnArgs a) {
   // the wave index is wave-uniform: through readfirstlane every quantity
   // derived from it (item, DMA block, base pointers) lives in SGPRs
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int idx = blockIdx.x * NW + w;
+  int idx = blockIdx.x * NW + w;
   if (idx >= a.n_items) return;
+  if (NW == 2 && a.n_items % kMhaWaves == 0) {
+    // longest first: the list deals the items ranked b, b + NB, b + 2 NB, b + 3 NB
+    // to workgroup b of NB four-wave workgroups
+    const int nb = a.n_items / kMhaWaves;
+    idx = idx % nb * kMhaWaves + idx / nb;
+  }
   attn_item<D, 32, NS, false, 1, 0>(a, a.items[idx], lds + w * NS * STAGE, 1, 0, threadIdx.x & 63);
 }
 
@@ -1087,16 +1093,17 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
 template <int D>
 hipError_t launch_bf16_d(const AttnArgs& a, int GW, bool merge, hipStream_t s) {
   if (GW == 1) {
-    constexpr int NS = 2, NW = kMhaWaves;
-    // Up to 512 items a workgroup is one wave, so that they spread over all the
-    // CUs (four to a workgroup leave half the chip idle at 512): LLaDA-8B heads,
-    // 128 items 31.4 -> 27.1 us, 256: 31.8 -> 27.7, 512: 38.5 -> 35.0; at 768 and
-    // 1024 four to a workgroup, dealt by length, are the faster (46.1 against
-    // 46.7, 59.0 against 60.6). 64-key tiles for the lone waves: 27.6, 29.1, 38.1.
-    if (a.n_items <= 512)
-      hipLaunchKernelGGL((k_attn_bf16_wave<D, NS, 1>), dim3(a.n_items), dim3(64), 0, s, a);
-    else
+    constexpr int NS = 2;
+    auto launch = [&](auto waves) {
+      constexpr int NW = decltype(waves)::value;
       hipLaunchKernelGGL((k_attn_bf16_wave<D, NS, NW>), dim3((a.n_items + NW - 1) / NW), dim3(64 * NW), 0, s, a);
+    };
+    if (a.n_items <= kMhaSpread)
+      launch(Num<1>{});
+    else if (a.n_items <= kMhaRound)
+      launch(Num<kMhaWaves>{});
+    else
+      launch(Num<2>{});
   } else if (D == 128 && GW <= 4 && a.pair) {   // at D = 64 the whole ring is half the LDS already
     hipLaunchKernelGGL((k_attn_bf16_pair<128, 2>), dim3(a.n_items), dim3(64 * GW), 0, s, a);
   } else if (GW < 4) {

@@ -407,6 +407,23 @@ def test_attention_two_workgroups_per_cu(ctx, L, Hq, Hkv):
         assert np.array_equal(one[0], full[i]), f"request {i} alone differs from in-batch"
 
 
+@pytest.mark.parametrize("n,H,D", [(16, 32, 64), (19, 27, 128), (32, 32, 64), (41, 25, 128), (33, 32, 128)])
+def test_attention_single_wave_workgroup_sizes(ctx, n, H, D):
+    # 512 items run one to a workgroup, 513 (not whole workgroups) and 1024 four,
+    # 1025 (a last workgroup of one) and 1056 (the dealt list read longest first)
+    # two; a request alone gives the same bits
+    rng = np.random.default_rng(n)
+    p = rng.integers(1, 300, n)
+    w = synth.custom(8, H, H, D, 10, "bf16", p.tolist(), [24] * n, rng.integers(0, 3, n).tolist(), kv_sigma=0.1,
+                     q_sigma=3.0)
+    _att(ctx, w, f"{n * H} single-wave items")
+    full, _, _, inp = run_attention(ctx, w, split=False)
+    for i in (0, n // 2, n - 1):
+        one, _, _, _ = run_attention(ctx, w, reqs=w.reqs[i:i + 1], q=inp["q"][i:i + 1], kn=inp["k_new"][i:i + 1],
+                                     vn=inp["v_new"][i:i + 1], kc=inp["k_cache"], vc=inp["v_cache"], split=False)
+        assert np.array_equal(one[0], full[i]), f"request {i} alone differs from in-batch"
+
+
 @pytest.mark.parametrize("L,Hq,Hkv,D", [(8, 2, 2, 64), (5, 6, 2, 64), (24, 3, 3, 128), (9, 14, 2, 128),
                                         (64, 2, 1, 128), (16, 1, 1, 256), (33, 2, 2, 256)])
 def test_attention_fp32_matrix_tiles(ctx, L, Hq, Hkv, D):
