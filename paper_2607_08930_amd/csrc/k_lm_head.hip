@@ -113,7 +113,11 @@ __device__ inline void wait_stages(int k) {
 // and five 256-row tiles the same rows took 1640 us. Four waves of 128 x 32 M
 // (two thirds of the LDS reads, accumulators in AGPRs, one wave per SIMD) took
 // 12% longer than eight.
-template <int M>
+//
+// ONCE: W is read by one row tile only and streams past the L2's other lines
+// with the non-temporal hint (calls on a LLaDA-8B head: 12 rows 193 -> 174 us, 64:
+// 193 -> 177, 125: 216.7 -> 212; Dream-7B head, 52 rows: 224 -> 208).
+template <int M, bool ONCE>
 __device__ inline void lm_tile(const LmArgs& a, uint16_t* ring, int vt, int r0, int count) {
   constexpr int HB = 4 * M;                              // 1 KiB blocks (16 rows) of the H tile
   constexpr int SLOT = kTile + HB * 512;                 // elements of a stage: W tile, then H tile
@@ -135,7 +139,12 @@ __device__ inline void lm_tile(const LmArgs& a, uint16_t* ring, int vt, int r0, 
   const uint32_t lds0 = lds_addr(ring);
   const uint16_t* wp = a.w + (int64_t)vt * (a.d / kLmKT) * kTile + w * 1024;   // next stage to issue
   uint32_t fill = lds0;                                                        // and its slot
-  auto issue_w = [&](int q) { dma16_sv(fill + (2 * w + q) * 1024, uniform64(wp + q * 512), (uint32_t)(lane * 16)); };
+  auto issue_w = [&](int q) {
+    if constexpr (ONCE)
+      dma16_sv_once(fill + (2 * w + q) * 1024, uniform64(wp + q * 512), (uint32_t)(lane * 16));
+    else
+      dma16_sv(fill + (2 * w + q) * 1024, uniform64(wp + q * 512), (uint32_t)(lane * 16));
+  };
   auto issue_h = [&](int q) {
     if (HB >= 8 * (q + 1) || (HB > 8 * q && w < 4)) dma16(fill + kTile * 2 + (w + 8 * q) * 1024, hp[q]);
   };
@@ -317,12 +326,19 @@ __global__ __launch_bounds__(512, 1) void k_lm_head(LmArgs a) {
   const int vt = (q / nact) * 8 + x, rt = q % nact;
   if (vt >= nvt) return;
   const int r0 = 64 * (rt * base + min(rt, extra));
-  switch (base + (rt < extra ? 1 : 0)) {
-    case 1: lm_tile<1>(a, ring, vt, r0, count); break;
-    case 2: lm_tile<2>(a, ring, vt, r0, count); break;
-    case 3: lm_tile<3>(a, ring, vt, r0, count); break;
-    default: lm_tile<4>(a, ring, vt, r0, count); break;
-  }
+  auto tile = [&](auto once) {
+    constexpr bool ONCE = decltype(once)::value != 0;
+    switch (base + (rt < extra ? 1 : 0)) {
+      case 1: lm_tile<1, ONCE>(a, ring, vt, r0, count); break;
+      case 2: lm_tile<2, ONCE>(a, ring, vt, r0, count); break;
+      case 3: lm_tile<3, ONCE>(a, ring, vt, r0, count); break;
+      default: lm_tile<4, ONCE>(a, ring, vt, r0, count); break;
+    }
+  };
+  if (nact == 1)
+    tile(Const<1>{});
+  else
+    tile(Const<0>{});
 }
 
 __device__ inline float wave_max(float v) {
