@@ -13,7 +13,7 @@
 //             compact [n][L] block state in increasing order and counts them.
 // k_lm_head   C^T = W H^T on v_mfma_f32_32x32x16_bf16 over 256 (vocabulary)
 //             x 64, 128, 192 or 256 (listed rows) tiles; K moves HBM -> LDS
-//             in 32-wide slices through a ring of 5 to 8 by direct DMA. Vocabulary is the MFMA M
+//             in 32-wide slices through a ring by direct DMA. Vocabulary is the MFMA M
 //             axis, so a lane holds one row's column of 16 logits per 32x32
 //             block: the epilogue reduces 32 logits per lane and row, exchanges
 //             once with the other half-wave and once through LDS. One DecPartial per (row,
@@ -98,14 +98,15 @@ __device__ inline void wait_stages(int k) {
   }
 }
 
-// One workgroup tile: 256 vocabulary entries x 64 M listed rows, M = 1..4.
+// One workgroup tile: 256 vocabulary entries x 64 M listed rows, M = 1..4, in
+// stages of KS slices of the contraction (each 32 wide).
 // Wave (wv, wr) = (w >> 1, w & 1) computes vocabulary rows 64 wv .. + 64 (two
 // 32-row blocks) x listed rows 32 M wr .. + 32 M.
 //
 // The matrix cores bound it, at the clock that their power leaves: the
 // operands of each half of a K slice (16 of its 32) are read from LDS beside
-// the MFMAs of the half before, and the slice's one barrier stands between the
-// halves, so that a wave leaves it with its next operands in registers and
+// the MFMAs of the half before, and the stage's one barrier stands before its
+// last half, so that a wave leaves it with its next operands in registers and
 // the slot that the barrier frees is refilled at once. The order is fixed by
 // scheduling fences: one MFMA, then one LDS read or one transfer.
 // Measured on a Dream-7B head (V = 152064, d = 3584), 1035 listed rows: 1065 us,
@@ -114,15 +115,21 @@ __device__ inline void wait_stages(int k) {
 // (two thirds of the LDS reads, accumulators in AGPRs, one wave per SIMD) took
 // 12% longer than eight.
 //
+// KS = 2 where a slice has few MFMAs between barriers (M <= 2 and d a multiple of
+// 64): 125 rows of a LLaDA-8B head 213 -> 202 us. At M = 3 and 4 it leaves two
+// stages of LDS and takes longer: 502 rows 492 -> 526, 1035 of a Dream-7B head
+// 1088 -> 1125.
+//
 // ONCE: W is read by one row tile only and streams past the L2's other lines
 // with the non-temporal hint (calls on a LLaDA-8B head: 12 rows 193 -> 174 us, 64:
 // 193 -> 177, 125: 216.7 -> 212; Dream-7B head, 52 rows: 224 -> 208).
-template <int M, bool ONCE>
+template <int M, bool ONCE, int KS>
 __device__ inline void lm_tile(const LmArgs& a, uint16_t* ring, int vt, int r0, int count) {
   constexpr int HB = 4 * M;                              // 1 KiB blocks (16 rows) of the H tile
-  constexpr int SLOT = kTile + HB * 512;                 // elements of a stage: W tile, then H tile
-  constexpr int NS = kLdsBytes / (SLOT * 2);             // 5 stages at M = 4, 8 at M = 1
-  constexpr int CHI = 2 + (HB + 7) / 8, CLO = 2 + HB / 8;   // transfers per stage of waves 0..3 and 4..7
+  constexpr int HT = HB * 512;                           // elements of the H tile of a slice
+  constexpr int SLOT = KS * (kTile + HT);                // elements of a stage: KS W tiles, then KS H tiles
+  constexpr int NS = kLdsBytes / (SLOT * 2);             // 5 stages at M = 4, 3 (of two slices) at M = 2
+  constexpr int CHI = KS * (2 + (HB + 7) / 8), CLO = KS * (2 + HB / 8);   // transfers per stage of waves 0..3 and 4..7
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
 
   // DMA: wave w issues W blocks 2w and 2w + 1 and H blocks w and w + 8 (where
@@ -139,19 +146,21 @@ __device__ inline void lm_tile(const LmArgs& a, uint16_t* ring, int vt, int r0, 
   const uint32_t lds0 = lds_addr(ring);
   const uint16_t* wp = a.w + (int64_t)vt * (a.d / kLmKT) * kTile + w * 1024;   // next stage to issue
   uint32_t fill = lds0;                                                        // and its slot
-  auto issue_w = [&](int q) {
+  auto issue_w = [&](int k, int q) {                     // slice k of the stage
+    const uint64_t src = uniform64(wp + k * kTile + q * 512);
     if constexpr (ONCE)
-      dma16_sv_once(fill + (2 * w + q) * 1024, uniform64(wp + q * 512), (uint32_t)(lane * 16));
+      dma16_sv_once(fill + k * kTile * 2 + (2 * w + q) * 1024, src, (uint32_t)(lane * 16));
     else
-      dma16_sv(fill + (2 * w + q) * 1024, uniform64(wp + q * 512), (uint32_t)(lane * 16));
+      dma16_sv(fill + k * kTile * 2 + (2 * w + q) * 1024, src, (uint32_t)(lane * 16));
   };
-  auto issue_h = [&](int q) {
-    if (HB >= 8 * (q + 1) || (HB > 8 * q && w < 4)) dma16(fill + kTile * 2 + (w + 8 * q) * 1024, hp[q]);
+  auto issue_h = [&](int k, int q) {
+    if (HB >= 8 * (q + 1) || (HB > 8 * q && w < 4))
+      dma16(fill + (KS * kTile + k * HT) * 2 + (w + 8 * q) * 1024, hp[q] + k * kLmKT);
   };
   auto issued = [&] {
-    wp += kTile;
-    hp[0] += kLmKT;
-    hp[1] += kLmKT;
+    wp += KS * kTile;
+    hp[0] += KS * kLmKT;
+    hp[1] += KS * kLmKT;
     fill = fill + SLOT * 2 == lds0 + NS * SLOT * 2 ? lds0 : fill + SLOT * 2;
   };
   auto wait_ahead = [&](int k) {
@@ -181,17 +190,22 @@ __device__ inline void lm_tile(const LmArgs& a, uint16_t* ring, int vt, int r0, 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[vb][rb][r] = 0.0f;
   bf16x8_t F[2][2 + M];                                  // per half: two W fragments, M H fragments
-  auto read = [&](const uint16_t* st, int s, int i) {
-    const uint16_t* p = i < 2 ? st + (64 * wv + 32 * i) * kLmKT : st + kTile + (32 * M * wr + 32 * (i - 2)) * kLmKT;
+  auto read = [&](const uint16_t* st, int hs, int i) {   // half hs of the stage's 2 KS
+    const int k = hs >> 1, s = hs & 1;
+    const uint16_t* p = i < 2 ? st + k * kTile + (64 * wv + 32 * i) * kLmKT
+                              : st + KS * kTile + k * HT + (32 * M * wr + 32 * (i - 2)) * kLmKT;
     F[s][i] = *reinterpret_cast<const bf16x8_t*>(p + off[s]);
   };
 
-  const int nk = a.d / kLmKT;
+  const int nk = a.d / (kLmKT * KS);                     // stages
   for (int t = 0; t < min(NS, nk); ++t) {
-    issue_w(0);
-    issue_w(1);
-    issue_h(0);
-    issue_h(1);
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      issue_w(k, 0);
+      issue_w(k, 1);
+      issue_h(k, 0);
+      issue_h(k, 1);
+    }
     issued();
   }
   wait_ahead(min(NS, nk) - 1);
@@ -200,36 +214,44 @@ __device__ inline void lm_tile(const LmArgs& a, uint16_t* ring, int vt, int r0, 
 #pragma unroll
   for (int i = 0; i < 2 + M; ++i) read(st, 0, i);
 
-  // Half s of stage t: 2 M MFMAs on F[s]; beside them the reads of the next
-  // half into F[s ^ 1], then the transfers of stage t + NS.
+  // Half hs of stage t: 2 M MFMAs on F[hs & 1]; beside them the reads of the next
+  // half (of the stage at `next`), and in the last half the transfers of stage t + NS.
   auto half = [&](auto half_tag, auto refill_tag, const uint16_t* next) {
-    constexpr int s = decltype(half_tag)::value, refill = decltype(refill_tag)::value;
+    constexpr int hs = decltype(half_tag)::value, refill = decltype(refill_tag)::value;
+    constexpr int s = hs & 1, nx = (hs + 1) % (2 * KS);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < 2 * M; ++i) {
       acc[i & 1][i >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F[s][i & 1], F[s][2 + (i >> 1)], acc[i & 1][i >> 1], 0, 0, 0);
-      if (i < 2 + M) read(next, s ^ 1, i);
+      if (i < 2 + M) read(next, nx, i);
       if (i == 2 * M - 1) {
 #pragma unroll
-        for (int k = 2 * M; k < 2 + M; ++k) read(next, s ^ 1, k);      // M = 1: three reads, two MFMAs
+        for (int k = 2 * M; k < 2 + M; ++k) read(next, nx, k);      // M = 1: three reads, two MFMAs
       }
-      if (refill && s == 1 && i >= 2 * M - 2) {
-        issue_w(i & 1);
-        issue_h(i & 1);
+      if (refill && nx == 0 && i >= 2 * M - 2) {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+          issue_w(k, i & 1);
+          issue_h(k, i & 1);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (refill && s == 1) issued();
+    if (refill && nx == 0) issued();
   };
   auto stage = [&](int t, auto refill_tag) {
     half(Const<0>{}, refill_tag, st);
+    if constexpr (KS == 2) {
+      half(Const<1>{}, refill_tag, st);
+      half(Const<2>{}, refill_tag, st);
+    }
     // Stage t + 1 has landed once only later ones are in flight. Past the
     // barrier every wave holds its last operands of stage t, so its slot is free.
     wait_ahead(refill_tag.value ? NS - 2 : max(nk - 2 - t, 0));
     barrier();
     st = st + SLOT == ring + NS * SLOT ? ring : st + SLOT;
     // after the last stage this reads a slot that nobody refills; the operands are not used
-    half(Const<1>{}, refill_tag, st);
+    half(Const<2 * KS - 1>{}, refill_tag, st);
   };
   int t = 0;
   for (; t + NS < nk; ++t) stage(t, Const<1>{});
@@ -328,11 +350,18 @@ __global__ __launch_bounds__(512, 1) void k_lm_head(LmArgs a) {
   const int r0 = 64 * (rt * base + min(rt, extra));
   auto tile = [&](auto once) {
     constexpr bool ONCE = decltype(once)::value != 0;
+    auto go = [&](auto m) {
+      constexpr int M = decltype(m)::value;
+      if constexpr (M <= 2) {
+        if (a.d % (2 * kLmKT) == 0) return lm_tile<M, ONCE, 2>(a, ring, vt, r0, count);
+      }
+      lm_tile<M, ONCE, 1>(a, ring, vt, r0, count);
+    };
     switch (base + (rt < extra ? 1 : 0)) {
-      case 1: lm_tile<1, ONCE>(a, ring, vt, r0, count); break;
-      case 2: lm_tile<2, ONCE>(a, ring, vt, r0, count); break;
-      case 3: lm_tile<3, ONCE>(a, ring, vt, r0, count); break;
-      default: lm_tile<4, ONCE>(a, ring, vt, r0, count); break;
+      case 1: go(Const<1>{}); break;
+      case 2: go(Const<2>{}); break;
+      case 3: go(Const<3>{}); break;
+      default: go(Const<4>{}); break;
     }
   };
   if (nact == 1)

@@ -125,12 +125,13 @@ def test_lm_head_row_tile_orders(ctx, n):
     assert band_ok(stats), stats
 
 
-@pytest.mark.parametrize("d", [96, 288, 352])
+@pytest.mark.parametrize("d", [64, 96, 288, 320, 352])
 @pytest.mark.parametrize("rows", [1, 64, 65, 128, 129, 192, 193, 256, 257, 577])
 def test_lm_head_row_tile_sizes(ctx, rows, d):
     # exact numbers of masked rows around the 64-row units that the row tiles
     # are made of; 3, 9 and 11 K slices are fewer than, about and more than the
-    # 5 to 8 stages of the ring
+    # 5 to 8 stages of the ring, 2 and 10 are 1 and 5 stages of two slices (of 3
+    # or 4) where a tile has at most 128 rows
     n, L, V = 20, 32, 520
     w = synth.custom(L, 2, 2, 16, V, "bf16", [3 + i for i in range(n)], [L] * n, [0] * n)
     wv = synth.gen_lm_weight(w, d)
