@@ -150,10 +150,11 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a, int jblocks) {
 // exp(x) for x <= about 88 from the hardware's exp2: the rounding of
 // x log2(e) and of log2(e) itself comes back as a first-order factor, so the
 // error stays near one ulp of the result for large |x| too. Arguments below
-// -200 (and -inf) give 0.
+// -200 (and -inf) give 0, NaN gives NaN (fmaxf would turn it into -200: the key
+// that holds it would drop out of the row unseen).
 __device__ inline float exp_f32(float x) {
   constexpr float kL2eHi = 1.44269502e+0f, kL2eLo = 1.92596299e-8f, kLn2 = 0.6931471805599453f;
-  x = fmaxf(x, -200.0f);
+  x = __builtin_elementwise_maximum(x, -200.0f);
   const float h = x * kL2eHi;
   const float lo = fmaf(x, kL2eLo, fmaf(x, kL2eHi, -h));
   const float e = __builtin_amdgcn_exp2f(h);
@@ -246,10 +247,13 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void k_attn_f32_mfma(AttnArgs a, i
     for (int dg = 0; dg < NDG; ++dg)
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[t][dg][e] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-  float mrun[NT], lsum[NT];
+  // running max, and the reference that the weights are taken against: the max,
+  // or 0 while every score so far is -inf (a key ruled out weighs 0, not NaN)
+  float mrun[NT], mref[NT], lsum[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     mrun[t] = -__builtin_inff();
+    mref[t] = 0.0f;
     lsum[t] = 0.0f;
   }
   // every LDS read of a slot has returned before its refill is issued
@@ -285,11 +289,11 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void k_attn_f32_mfma(AttnArgs a, i
           if (tb + 4 * q + r >= len) s[t][r] = -__builtin_inff();
       }
       const float mx = quarter_max(fmaxf(fmaxf(s[t][0], s[t][1]), fmaxf(s[t][2], s[t][3])));
-      // lazy rescale: the reference max moves only when a score exceeds it by
-      // 8 (the tile holds at least one key, so mx is finite)
+      // lazy rescale: the max moves only when a score exceeds it by 8
       if (__builtin_amdgcn_ballot_w64(mx > mrun[t] + 8.0f)) {
         const float mnew = fmaxf(mrun[t], mx);
-        const float alpha = exp_f32(mrun[t] - mnew);
+        mref[t] = mnew == -__builtin_inff() ? 0.0f : mnew;
+        const float alpha = exp_f32(mrun[t] - mref[t]);
         lsum[t] *= alpha;
 #pragma unroll
         for (int dg = 0; dg < NDG; ++dg)
@@ -299,7 +303,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void k_attn_f32_mfma(AttnArgs a, i
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        s[t][r] = exp_f32(s[t][r] - mrun[t]);
+        s[t][r] = exp_f32(s[t][r] - mref[t]);
         lsum[t] += s[t][r];
       }
     }
@@ -344,7 +348,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void k_attn_f32_mfma(AttnArgs a, i
     float l = 0.0f;
 #pragma unroll
     for (int k = 0; k < NW; ++k) l += sml[1][k][16 * t + n] * exp_f32(sml[0][k][16 * t + n] - M);
-    const float wgt = exp_f32(mrun[t] - M) / l;   // 0 for a wave without tiles (mrun = -inf)
+    const float wgt = exp_f32(mrun[t] - M) / l;   // 0 for a wave without a finite score, NaN if no wave has one
 #pragma unroll
     for (int dg = 0; dg < NDG; ++dg)
 #pragma unroll

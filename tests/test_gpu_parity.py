@@ -439,6 +439,46 @@ def test_attention_fp32_matrix_tiles(ctx, L, Hq, Hkv, D):
     _att(ctx, at_start, f"fp32 L{L} G{Hq // Hkv} D{D} block first")
 
 
+@pytest.mark.parametrize("D", [64, 128, 256])
+def test_attention_fp32_nan_and_ruled_out_keys(ctx, D):
+    # a key whose score is NaN makes the whole row NaN, and keys scored -inf
+    # weigh nothing, wherever they fall in the waves' 16-key tiles: a cached and
+    # a fresh NaN key in a wave's first and in a later tile, a tile all of -inf
+    # (a wave's only one, and the first of several), a tile of scores that
+    # overflow to -inf for some queries and not for others, NaN queries, and
+    # scores of +inf; request 0 has none
+    L = 8
+    p = [290, 290, 290, 290, 40, 290, 290, 290, 290]
+    w = synth.custom(L, 2, 2, D, 10, "f32", p, [8] * len(p), [0] * len(p), q_sigma=1.0)
+    q, (kn, vn), (kc, vc) = synth.gen_q(w), synth.gen_kv_new(w), synth.gen_cache(w)
+    q = np.abs(q) + np.float32(0.01)
+
+    def key(i, t):
+        return kc[w.reqs["row"][i], :, w.reqs["off"][i] + t]
+
+    key(1, 3)[0, 5] = np.nan                      # head 0, a wave's first tile
+    key(2, 280)[1, D - 1] = np.nan                # head 1, a later tile
+    kn[3, 5, 0, 7] = np.nan                       # a fresh key
+    for t in range(16, 32):
+        key(4, t)[:] = -np.inf                    # the only tile of wave 1
+        key(5, t)[:] = -np.inf                    # its first of several
+        key(6, t)[:, 0] = -3e38
+    q[6, ::2, :, 0] = 20.0
+    q[6, 1::2, :, 0] = 2e-38
+    q[7, 2, 1, 0] = np.nan
+    key(8, 100)[0, 0] = np.inf
+    say(f"[attention fp32 NaN and ruled-out keys D{D}]")
+    with np.errstate(all="ignore"):
+        ref, _, _ = oracle.dual_cache_block_attention(w.reqs, L, q, kn, vn, kc, vc, dtype="f32")
+        assert np.isneginf((key(6, 20)[0].astype(np.float32) * q[6, 0, 0]).sum(dtype=np.float32))
+    out, _, _, _ = run_attention(ctx, w, q=q, kn=kn, vn=vn, kc=kc, vc=vc)
+    for i in range(w.n):
+        np.testing.assert_array_equal(np.isnan(out[i]), np.isnan(ref[i]), err_msg=f"request {i}")
+        assert np.nanmax(np.abs(out[i] - ref[i])) <= ATT_TOL["f32"], f"request {i}"
+    assert np.isnan(ref[[1, 3]][:, :, 0]).all() and np.isnan(ref[2][:, 1]).all() and np.isnan(ref[7][2, 1]).all()
+    assert np.isfinite(ref[[0, 4, 5, 6]]).all()
+
+
 def test_attention_long_rows(ctx):
     # rows far longer than the workloads': 16 384 keys for MHA (512 tiles of a
     # single wave's stream) and 12 000 for a 7-head group, next to short rows
