@@ -170,6 +170,8 @@ __device__ inline float quarter_max(float v) {
   return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
 }
 
+__device__ const float kZeros[4] __attribute__((aligned(16))) = {0.0f, 0.0f, 0.0f, 0.0f};
+
 template <int D, int NT, int NW>
 __global__ __launch_bounds__(64 * NW, NW / 4) void k_attn_f32_mfma(AttnArgs a, int rtiles) {
   constexpr int KT = 16;                          // keys per tile
@@ -213,8 +215,11 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void k_attn_f32_mfma(AttnArgs a, i
       if (whole) {
         dma16_sv_once(dst, uniform64(cb + (int64_t)tb * D), (uint32_t)(row * D + chunk * 4) * 4u);
       } else {
-        const int t = min(tb + row, len - 1);                 // rows past the end repeat a valid key (masked later)
-        dma16_once(dst, (t >= bs && t < be ? nb + (int64_t)(t - bs) * fstride : cb + (int64_t)t * D) + chunk * 4);
+        // rows past the end: a valid key again (its score is masked), and values
+        // of 0 (a valid key's may be infinite, and 0 times that is NaN)
+        const int t = min(tb + row, len - 1);
+        const float* src = (t >= bs && t < be ? nb + (int64_t)(t - bs) * fstride : cb + (int64_t)t * D) + chunk * 4;
+        dma16_once(dst, tensor && tb + row >= len ? kZeros : src);
       }
     }
   };

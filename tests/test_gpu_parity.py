@@ -479,6 +479,24 @@ def test_attention_fp32_nan_and_ruled_out_keys(ctx, D):
     assert np.isfinite(ref[[0, 4, 5, 6]]).all()
 
 
+@pytest.mark.parametrize("D", [64, 128, 256])
+def test_attention_fp32_infinite_last_value(ctx, D):
+    # an infinite value of a row's last key gives an infinite output, also where
+    # the row ends inside a 16-key tile (of one tile, and of several per wave)
+    p = [3, 8, 56, 290, 296]
+    w = synth.custom(8, 2, 2, D, 10, "f32", p, [8] * len(p), [0] * len(p))
+    q, (kn, vn), (kc, vc) = synth.gen_q(w), synth.gen_kv_new(w), synth.gen_cache(w)
+    vn[:, 7, 0, 3] = np.inf
+    vn[:, 7, 1, D - 1] = -np.inf
+    say(f"[attention fp32 infinite last value D{D}]")
+    ref, _, _ = oracle.dual_cache_block_attention(w.reqs, w.L, q, kn, vn, kc, vc, dtype="f32")
+    out, _, _, _ = run_attention(ctx, w, q=q, kn=kn, vn=vn, kc=kc, vc=vc)
+    assert np.isposinf(ref[:, :, 0, 3]).all() and np.isneginf(ref[:, :, 1, D - 1]).all() and not np.isnan(ref).any()
+    fin = np.isfinite(ref)
+    np.testing.assert_array_equal(out[~fin], ref[~fin])
+    assert np.isfinite(out[fin]).all() and np.abs(out[fin] - ref[fin]).max() <= ATT_TOL["f32"]
+
+
 def test_attention_long_rows(ctx):
     # rows far longer than the workloads': 16 384 keys for MHA (512 tiles of a
     # single wave's stream) and 12 000 for a 7-head group, next to short rows
