@@ -10,7 +10,6 @@
 #include <functional>
 #include <memory>
 #include <mutex>
-#include <queue>
 #include <string>
 #include <vector>
 
@@ -354,21 +353,25 @@ void interleave_waves(AttnItem* items, AttnItem* tmp, size_t N) {
 
 void attention_items_into(AttnItem* items, AttnItem* tmp, const bs_req_desc* reqs, int n, int L, int Hq, int Hkv) {
   const int split = attention_split(L, Hq, Hkv);
-  size_t N = 0;
+  // a request's items are alike but for head and row block: sort one of each
   for (int i = 0; i < n; ++i) {
     const Geo gq = geo_of(reqs[i], L);
-    for (int h = 0; h < Hkv; ++h)
-      for (int rb = 0; rb < split; ++rb)
-        items[N++] = AttnItem{i, h, gq.len, gq.s, gq.B, reqs[i].row, reqs[i].off, rb, 0,
-                              (gq.len + kAttnTile - 1) / kAttnTile, -1, 0};
+    tmp[i] = AttnItem{i, 0, gq.len, gq.s, gq.B, reqs[i].row, reqs[i].off, 0, 0,
+                      (gq.len + kAttnTile - 1) / kAttnTile, -1, 0};
   }
   // longest first; equal lengths keep the (request, head, row block) order
-  std::sort(items, items + N, [](const AttnItem& x, const AttnItem& y) {
-    if (x.len != y.len) return x.len > y.len;
-    if (x.req != y.req) return x.req < y.req;
-    if (x.kvh != y.kvh) return x.kvh < y.kvh;
-    return x.rb < y.rb;
+  std::sort(tmp, tmp + n, [](const AttnItem& x, const AttnItem& y) {
+    return x.len != y.len ? x.len > y.len : x.req < y.req;
   });
+  size_t N = 0;
+  for (int i = 0; i < n; ++i)
+    for (int h = 0; h < Hkv; ++h)
+      for (int rb = 0; rb < split; ++rb) {
+        AttnItem& it = items[N++];
+        it = tmp[i];
+        it.kvh = h;
+        it.rb = rb;
+      }
   if (Hq == Hkv && L <= 32) interleave_waves(items, tmp, N);
 }
 
@@ -428,36 +431,62 @@ int waves_per_item(int L, int Hq, int Hkv) {
   return G * (G * RB > 8 ? 1 : RB);
 }
 
-// Estimated launch time (tiles) of work items of `tiles` tiles each (sorts
-// `tiles`). Items go to workgroups as the launch will place them (a group of
-// ps.group items, interleaved like interleave_waves when they fill whole
-// workgroups); a workgroup holds its CU until its longest item is done.
-double launch_estimate(std::vector<int>& tiles, const PlanShape& ps) {
-  std::sort(tiles.begin(), tiles.end(), std::greater<int>());
-  const size_t N = tiles.size(), G = (size_t)ps.group;
-  const size_t NB = (N + G - 1) / G;
-  double total = 0.0;
-  for (int t : tiles) total += kPieceOverhead + t;
-  std::priority_queue<double, std::vector<double>, std::greater<double>> cu;
-  for (int i = 0; i < kPlanCUs; ++i) cu.push(0.0);
-  double end = 0.0;
-  for (size_t b = 0; b < NB; ++b) {
-    // sorted list: the workgroup's longest item is its first
-    const int longest = N % G == 0 ? tiles[b] : tiles[b * G];
-    const double x = cu.top() + kPieceOverhead + longest;
-    cu.pop();
-    cu.push(x);
-    end = std::max(end, x);
+// `count` work items of `tiles` tiles each.
+struct Run {
+  int tiles, count;
+};
+
+// The runs of a batch's whole rows: one per request, in request order.
+std::vector<Run> row_runs(const bs_req_desc* reqs, int n, int L, int Hq, int Hkv) {
+  const int per_req = Hkv * attention_split(L, Hq, Hkv);
+  std::vector<Run> runs((size_t)n);
+  for (int i = 0; i < n; ++i)
+    runs[i] = Run{std::max((geo_of(reqs[i], L).len + kAttnTile - 1) / kAttnTile, 0), per_req};
+  return runs;
+}
+
+// Estimated launch time (tiles) of the work items in `runs` (sorts them).
+// Items go to workgroups of ps.group, interleaved like interleave_waves when
+// they fill whole workgroups; a workgroup holds its CU until its longest item
+// is done. A call with new descriptors waits for this, so it counts runs and
+// not items: bs_attention_workspace_bytes of 4 LLaDA-8B requests 35 -> 3.7 us, of
+// 32: 67 -> 3.2 us (seven estimates that sorted and placed every item, before).
+double launch_estimate(std::vector<Run>& runs, const PlanShape& ps) {
+  std::sort(runs.begin(), runs.end(), [](const Run& x, const Run& y) { return x.tiles > y.tiles; });
+  size_t N = 0;
+  double total = 0.0;                     // whole numbers: exact in any order
+  for (const Run& r : runs) {
+    N += (size_t)r.count;
+    total += (double)r.count * (kPieceOverhead + r.tiles);
+  }
+  const size_t G = (size_t)ps.group, NB = (N + G - 1) / G;
+  const size_t step = N % G == 0 ? 1 : G;   // rank of workgroup b's longest item: b * step
+  // one workgroup per CU at first: the longest of them ends last
+  double end = NB ? kPieceOverhead + runs[0].tiles : 0.0;
+  if (NB > (size_t)kPlanCUs) {
+    double cu[kPlanCUs];                    // min-heap of the CUs' loads
+    size_t run = 0, run_end = (size_t)runs[0].count;
+    auto load = [&](size_t b) {
+      while (b * step >= run_end) run_end += (size_t)runs[++run].count;
+      return kPieceOverhead + runs[run].tiles;
+    };
+    for (int b = 0; b < kPlanCUs; ++b) cu[kPlanCUs - 1 - b] = load((size_t)b);   // ascending: a heap
+    for (size_t b = (size_t)kPlanCUs; b < NB; ++b) {
+      std::pop_heap(cu, cu + kPlanCUs, std::greater<double>());
+      cu[kPlanCUs - 1] += load(b);
+      end = std::max(end, cu[kPlanCUs - 1]);
+      std::push_heap(cu, cu + kPlanCUs, std::greater<double>());
+    }
   }
   return std::max(end, ps.full_load * total / ((double)kPlanCUs * G));
 }
 
-// Largest piece (tiles) of the best plan for rows of nt[i] tiles, or 0 for no cut.
-int split_cap(const std::vector<int>& nt, const PlanShape& ps) {
-  if (nt.empty()) return 0;
+// Largest piece (tiles) of the best plan for the rows in `rows`, or 0 for no cut.
+int split_cap(const std::vector<Run>& rows, const PlanShape& ps) {
+  if (rows.empty()) return 0;
   double total = 0.0;
-  for (int t : nt) total += t + kPieceOverhead;
-  std::vector<int> w(nt);
+  for (const Run& r : rows) total += (double)r.count * (r.tiles + kPieceOverhead);
+  std::vector<Run> w(rows);
   const double whole = launch_estimate(w, ps);
   const int lb = (int)std::ceil(total / ((double)kPlanCUs * ps.group));
   if (whole <= ps.full_load * lb + kMergeFixed) return 0;    // no plan can gain
@@ -467,15 +496,17 @@ int split_cap(const std::vector<int>& nt, const PlanShape& ps) {
     const int cap = T - (int)kPieceOverhead;
     if (cap < 2) continue;
     w.clear();
-    int parts = 0;
-    for (int t : nt) {
-      if (t <= cap) {
-        w.push_back(t);
+    int parts = 0, full = 0;
+    for (const Run& r : rows) {
+      if (r.tiles <= cap) {
+        w.push_back(r);
         continue;
       }
-      for (int r = t; r > 0; r -= cap) w.push_back(std::min(r, cap));
-      parts += (t + cap - 1) / cap;
+      full += r.tiles / cap * r.count;
+      if (r.tiles % cap) w.push_back(Run{r.tiles % cap, r.count});
+      parts += (r.tiles + cap - 1) / cap * r.count;
     }
+    if (full) w.push_back(Run{cap, full});
     const double est = launch_estimate(w, ps) + kMergeFixed + ps.per_part * parts;
     if (est < best) {
       best = est;
@@ -486,18 +517,21 @@ int split_cap(const std::vector<int>& nt, const PlanShape& ps) {
 }
 
 // Cuts the whole rows `items` (as attention_items_into leaves them) into
-// pieces of at most `cap` tiles, sorted longest first; a row's pieces take
+// pieces of at most `cap` (> 0) tiles, sorted longest first; a row's pieces take
 // consecutive partial slots, and `merges` lists the rows that were cut.
 // Returns the number of partial slots.
 int split_items(const std::vector<AttnItem>& items, int cap, std::vector<AttnItem>& pieces,
                 std::vector<AttnMerge>& merges) {
+  std::vector<AttnItem> cut;
+  std::vector<size_t> at((size_t)cap + 1, 0);   // pieces of t tiles, then where the next of them goes
+  auto tiles = [](const AttnItem& x) { return (size_t)std::max(x.t1 - x.t0, 0); };
   int parts = 0;
-  pieces.clear();
   merges.clear();
   for (const AttnItem& it : items) {
     const int nt = it.t1 - it.t0;
-    if (cap <= 0 || nt <= cap) {
-      pieces.push_back(it);
+    if (nt <= cap) {
+      cut.push_back(it);
+      ++at[tiles(it)];
       continue;
     }
     const int np = (nt + cap - 1) / cap;
@@ -507,13 +541,19 @@ int split_items(const std::vector<AttnItem>& items, int cap, std::vector<AttnIte
       p.t0 = k * cap;
       p.t1 = std::min(nt, (k + 1) * cap);
       p.part = parts + k;
-      pieces.push_back(p);
+      cut.push_back(p);
+      ++at[tiles(p)];
     }
     parts += np;
   }
-  std::stable_sort(pieces.begin(), pieces.end(), [](const AttnItem& x, const AttnItem& y) {
-    return x.t1 - x.t0 > y.t1 - y.t0;
-  });
+  size_t first = 0;                             // pieces of equal length keep their order
+  for (size_t t = at.size(); t-- > 0;) {
+    const size_t n = at[t];
+    at[t] = first;
+    first += n;
+  }
+  pieces.resize(cut.size());
+  for (const AttnItem& p : cut) pieces[at[tiles(p)]++] = p;
   return parts;
 }
 
@@ -553,11 +593,7 @@ void attention_blob(Blob& blob, const bs_req_desc* reqs, int n, int L, int Hq, i
     std::vector<AttnItem> items(N), tmp(N);
     attention_items_into(items.data(), tmp.data(), reqs, n, L, Hq, Hkv);
     int cap = 0;
-    if (split) {
-      std::vector<int> nt(N);
-      for (size_t i = 0; i < N; ++i) nt[i] = items[i].t1 - items[i].t0;
-      cap = split_cap(nt, plan_shape(L, Hq, Hkv));
-    }
+    if (split) cap = split_cap(row_runs(reqs, n, L, Hq, Hkv), plan_shape(L, Hq, Hkv));
     std::vector<AttnItem> pieces;
     std::vector<AttnMerge> merges;
     const int parts = cap > 0 ? split_items(items, cap, pieces, merges) : 0;
@@ -940,16 +976,12 @@ size_t bs_attention_workspace_bytes(const bs_req_desc* reqs, int n, int L, int H
                                     bs_dtype dt) {
   if (!reqs || n <= 0 || dt != BS_BF16 || L < 1 || L > 64 || Hkv < 1 || Hq < Hkv || Hq % Hkv || (D != 64 && D != 128))
     return 0;
-  const size_t N = attention_item_count(n, L, Hq, Hkv, dt);
-  std::vector<AttnItem> items(N), tmp(N);
-  attention_items_into(items.data(), tmp.data(), reqs, n, L, Hq, Hkv);
-  std::vector<int> nt(N);
-  for (size_t i = 0; i < N; ++i) nt[i] = std::max(items[i].t1 - items[i].t0, 0);
-  const int cap = split_cap(nt, plan_shape(L, Hq, Hkv));
+  const std::vector<Run> rows = row_runs(reqs, n, L, Hq, Hkv);
+  const int cap = split_cap(rows, plan_shape(L, Hq, Hkv));
   int parts = 0;
   if (cap > 0)
-    for (int t : nt)
-      if (t > cap) parts += (t + cap - 1) / cap;
+    for (const Run& r : rows)
+      if (r.tiles > cap) parts += (r.tiles + cap - 1) / cap * r.count;
   return part_bytes(parts, L, Hq, Hkv, D);
 }
 

@@ -2,7 +2,11 @@
 every row's 64-key tiles are covered exactly once, cut rows take consecutive
 partial slots, the launch order is longest piece first, and the workspace
 queries size exactly the plan's partial slots."""
+import heapq
+import math
+
 import numpy as np
+import pytest
 
 import synth
 import paper_2607_08930_amd as bs
@@ -150,6 +154,69 @@ def test_plan_edge_cases():
     items, n_parts = bs.bs_attention_work_list(w.reqs, w.L, w.Hq, w.Hkv, w.D, bs.BS_BF16, 1)
     _check_plan(w, items, n_parts)
     assert bs.bs_attention_workspace_bytes(w.reqs, w.L, w.Hq, w.Hkv, w.D, bs.BS_F32) == 0
+
+
+def _estimate(tiles, group, full_load):
+    """The list schedule item by item: workgroups of ``group`` items on the
+    least-loaded of 256 CUs, longest first, and the machine-wide bound."""
+    t = sorted(tiles, reverse=True)
+    heap, end = [0.0] * 256, 0.0
+    for b in range(-(-len(t) // group)):
+        x = heapq.heappop(heap) + 2.0 + (t[b] if len(t) % group == 0 else t[b * group])
+        heapq.heappush(heap, x)
+        end = max(end, x)
+    return max(end, full_load * sum(2.0 + x for x in t) / (256.0 * group))
+
+
+def _best_cap(tiles, group, full_load, per_part):
+    whole = best = _estimate(tiles, group, full_load)
+    lb = math.ceil(sum(2.0 + x for x in tiles) / (256.0 * group))
+    cap = 0
+    if whole <= full_load * lb + 3.0:
+        return 0
+    for c in range(max(lb - 2, 2), lb + 4):
+        cut = [x for t in tiles for x in ([t] if t <= c else [c] * (t // c) + ([t % c] if t % c else []))]
+        est = _estimate(cut, group, full_load) + 3.0 + per_part * sum(-(-t // c) for t in tiles if t > c)
+        if est < best:
+            best, cap = est, c
+    return cap
+
+
+@pytest.mark.parametrize("L,Hq,Hkv,n,hi", [(32, 28, 4, 24, 1000), (32, 28, 4, 100, 4000), (64, 28, 4, 9, 3000),
+                                           (48, 8, 8, 40, 2000), (32, 32, 32, 3, 700), (32, 32, 32, 5, 700),
+                                           (32, 32, 32, 40, 5000), (8, 25, 25, 17, 9000), (24, 3, 3, 90, 300),
+                                           (16, 1, 1, 1, 20000)])
+def test_plan_matches_the_estimate_item_by_item(L, Hq, Hkv, n, hi):
+    # lists of fewer workgroups than CUs and of more, whole and not whole
+    # workgroups, long rows among short and rows all alike: the plan cuts where
+    # the estimate over single items says, and the cut list is the whole one
+    # with every row in pieces of that length, longest first
+    for seed in range(6):
+        rng = np.random.default_rng(seed)
+        p = rng.integers(0, hi, n) if seed else np.full(n, hi)
+        if seed > 3:
+            p[n // 2] = 4 * hi
+        w = synth.custom(L, Hq, Hkv, 128, 10, "bf16", p.tolist(), [100] * n, [0] * n)
+        single = Hq == Hkv and L <= 32
+        whole, _ = bs.bs_attention_work_list(w.reqs, w.L, w.Hq, w.Hkv, w.D, bs.BS_BF16, 0)
+        cap = _best_cap((whole[:, 4] - whole[:, 3]).tolist(), 4 if single else 1, 2.0 if single else 1.3,
+                        0.01 if single else 0.02)
+        want, parts = [], 0
+        for req, kvh, rb, t0, t1, _ in whole.tolist():
+            if cap == 0 or t1 <= cap:
+                want.append((req, kvh, rb, t0, t1, -1))
+                continue
+            for t in range(0, t1, cap):
+                want.append((req, kvh, rb, t, min(t + cap, t1), parts))
+                parts += 1
+        if cap:
+            want.sort(key=lambda x: x[3] - x[4])
+            if single and len(want) % 4 == 0:
+                nb = len(want) // 4
+                want = [want[j * nb + b] for b in range(nb) for j in range(4)]
+        items, n_parts = bs.bs_attention_work_list(w.reqs, w.L, w.Hq, w.Hkv, w.D, bs.BS_BF16, 1)
+        assert n_parts == parts and items.tolist() == [list(x) for x in want]
+        assert bs.bs_attention_workspace_bytes(w.reqs, w.L, w.Hq, w.Hkv, w.D, bs.BS_BF16) == _ws_bytes(w, parts)
 
 
 def test_work_list_rejects_unsupported_shapes():
