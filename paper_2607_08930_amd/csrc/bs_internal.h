@@ -97,15 +97,18 @@ struct AttnArgs {
 
 // Waves (independent items) per workgroup of the single-wave bf16 kernel, whose
 // 256 CUs hold four each: four, dealt by length, for lists that the chip holds
-// at once; one for lists of at most kMhaSpread items, so that they spread over
-// the CUs; two, longest first, for lists longer than kMhaRound, where a CU takes
-// the next workgroup when one is done (four to a workgroup wait for the longest
-// of them). Measured on LLaDA-8B heads (us, four to a workgroup -> as here): 128
-// items 31.4 -> 27.1, 256: 31.8 -> 27.7, 512: 38.5 -> 35.0; 1152: 81.6 -> 68.8,
-// 1536: 94.4 -> 88.0, 2048: 113.4 -> 109.8, 3072: 171 -> 165. Between the lines
-// four are the faster: 640 items 41.1 (one 41.2, two 44.1), 768: 46.1 (46.7,
-// 48.5), 1024: 58.4 (60.6, 59.2). One to a workgroup above: 1152: 69.1, 1536:
-// 90.8, 3072: 169.9.
+// at once; one, longest first, for lists of at most kMhaSpread items, so that
+// they spread over the CUs; two, longest first, for lists longer than kMhaRound,
+// where a CU takes the next workgroup when one is done (four to a workgroup wait
+// for the longest of them). Measured on LLaDA-8B heads (us, four to a workgroup
+// -> as here): 192 items 34.0 -> 27.4, 256: 32.4 -> 27.5, 384: 35.9 -> 30.0, 512:
+// 39.2 -> 34.9; 1152: 81.6 -> 68.8, 1536: 94.4 -> 88.0, 2048: 113.4 -> 109.8, 3072:
+// 171 -> 165. Between the lines four are about as fast or faster: 544 items 39.6
+// (one 38.8), 640: 41.2 (one 41.0, two 44.1), 768: 46.4 (one 46.5, two 48.5), 896:
+// 53.3 (one 54.6), 1024: 59.2 (one 59.1, two 59.2). One to a workgroup above:
+// 1152: 69.1, 1536: 90.8, 3072: 169.9. At D = 64, where a CU holds eight such
+// waves, the same lines: 256 items 21.6 -> 21.4, 512: 24.3 -> 23.5, 1056: 41.9 ->
+// 36.6, 1536: 50.4 -> 45.5, 2048: 59.2 -> 59.4.
 constexpr int kMhaWaves = 4;
 constexpr int kMhaSpread = 512;
 constexpr int kMhaRound = 1024;

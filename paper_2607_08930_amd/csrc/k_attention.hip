@@ -1064,9 +1064,11 @@ __global__ __launch_bounds__(64 * NW, 1) void k_attn_bf16_wave(AttnArgs a) {
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int idx = blockIdx.x * NW + w;
   if (idx >= a.n_items) return;
-  if (NW == 2 && a.n_items % kMhaWaves == 0) {
+  if (NW < kMhaWaves && a.n_items % kMhaWaves == 0) {
     // longest first: the list deals the items ranked b, b + NB, b + 2 NB, b + 3 NB
-    // to workgroup b of NB four-wave workgroups
+    // to workgroup b of NB four-wave workgroups. Taken as it stands by one-wave
+    // workgroups (b on XCD b % 8) it would give two XCDs the longest quarter of
+    // the items and two the shortest.
     const int nb = a.n_items / kMhaWaves;
     idx = idx % nb * kMhaWaves + idx / nb;
   }
