@@ -427,16 +427,57 @@ def test_attention_single_wave_workgroup_sizes(ctx, n, H, D):
 @pytest.mark.parametrize("L,Hq,Hkv,D", [(8, 2, 2, 64), (5, 6, 2, 64), (24, 3, 3, 128), (9, 14, 2, 128),
                                         (64, 2, 1, 128), (16, 1, 1, 256), (33, 2, 2, 256)])
 def test_attention_fp32_matrix_tiles(ctx, L, Hq, Hkv, D):
-    # the fp32 matrix-core kernel deals a row's 16-key tiles to its 2 or 4
-    # waves: rows from one key to several tiles per wave, whole and ragged,
-    # with the fresh block last and first, and query groups (g * L + j) of one
-    # 16-row tile, of 32-row tiles with a remainder, and of several tiles
+    # the fp32 matrix-core kernel deals a row's 16-key tiles to its 8 waves (4 at
+    # D = 256): rows from one key to two tiles per wave (four at D = 256), whole
+    # and ragged, with the fresh block last and first, and query groups
+    # (g * L + j) of one 16-row tile, of 32-row tiles with a remainder, and of
+    # several tiles
     lens = [1, 2, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 160, 193]
     at_end = synth.custom(L, Hq, Hkv, D, 10, "f32", [max(t - L, 0) for t in lens], [min(t, L) for t in lens],
                           [0] * len(lens), q_sigma=2.0)
     at_start = synth.custom(L, Hq, Hkv, D, 10, "f32", [0] * len(lens), lens, [0] * len(lens), variant=1)
     _att(ctx, at_end, f"fp32 L{L} G{Hq // Hkv} D{D} block last")
     _att(ctx, at_start, f"fp32 L{L} G{Hq // Hkv} D{D} block first")
+
+
+def _fp32_reference_rises(w, waves):
+    """(query, wave) pairs whose running max is raised by more than 8 in a tile
+    after the wave's first: the sums and outputs so far are rescaled there."""
+    q, (kn, _), (kc, _) = synth.gen_q(w), synth.gen_kv_new(w), synth.gen_cache(w)
+    rises = 0
+    for i, r in enumerate(w.reqs):
+        t = oracle.geometry(r, w.L)
+        for h in range(w.Hq):
+            c = h // (w.Hq // w.Hkv)
+            keys = kc[t.row, c, t.off:t.off + t.len].astype(np.float64)
+            keys[t.s:t.e] = kn[i, :t.B, c]
+            z = q[i, :t.B, h].astype(np.float64) @ keys.T / np.sqrt(w.D)
+            top = [z[:, k:k + 16].max(1) for k in range(0, t.len, 16)]
+            for wave in range(waves):
+                ref = None
+                for m in top[wave::waves]:
+                    if ref is None:
+                        ref = m.copy()
+                        continue
+                    up = m > ref + 8.0
+                    rises += int(up.sum())
+                    ref = np.where(up, m, ref)
+    return rises
+
+
+@pytest.mark.parametrize("L,Hq,Hkv,D", [(8, 2, 2, 64), (32, 4, 4, 128), (24, 6, 2, 128), (32, 2, 1, 64), (16, 2, 2, 256)])
+def test_attention_fp32_rows_of_many_tiles(ctx, L, Hq, Hkv, D):
+    # three to six tiles per wave (6 to 12 at D = 256), whole and ragged, with
+    # scores of a spread (std 4.5) that raises the waves' reference max in later
+    # tiles, so sums and outputs that are not zero are rescaled. Scores reach 20
+    # and their fp32 sums of up to 256 products are off by about 4e-6, which is
+    # the relative error of a weight; values of 0.3 keep the outputs' within
+    # ATT_TOL
+    lens = [385, 400, 512, 641, 733, 768]
+    w = synth.custom(L, Hq, Hkv, D, 10, "f32", [t - 2 * L for t in lens], [2 * L] * len(lens), [0, 1, 0, 1, 1, 0],
+                     q_sigma=15.0, kv_sigma=0.3)
+    assert _fp32_reference_rises(w, 4 if D == 256 else 8) >= 8
+    _att(ctx, w, f"fp32 L{L} G{Hq // Hkv} D{D} many tiles")
 
 
 @pytest.mark.parametrize("D", [64, 128, 256])
