@@ -255,7 +255,7 @@ def step_parity(w, host, got, ref):
 
 KERNEL_SOURCES = {   # kernel name prefix -> sources whose change voids its counter-derived traffic
     "k_attn_bf16": ["k_attention.hip", "bs_merge.h", "bs_internal.h", "bs_lds.h"],
-    "k_attn_f32": ["k_attention.hip", "bs_internal.h"],
+    "k_attn_f32": ["k_attention.hip", "bs_internal.h", "bs_lds.h"],
     "k_lm_head": ["k_lm_head.hip", "bs_internal.h", "bs_lds.h"],
     "k_refresh_attn": ["k_refresh.hip", "bs_refresh.h", "bs_internal.h", "bs_lds.h"],
     "k_refresh_kv": ["k_refresh.hip", "bs_refresh.h", "bs_internal.h"],

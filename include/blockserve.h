@@ -182,14 +182,14 @@ int bs_scatter_active_blocks_n(bs_ctx* ctx, const bs_req_desc* reqs, int n, int 
  * ws: NULL, or a device workspace of ws_bytes bytes (contents on entry
  * ignored). Straggler handling (split-KV; the paper's straggler effect,
  * Introduction and RQ2): the BS_BF16 kernels hold a fixed number of rows at
- * once (one workgroup of G * ceil(L / 32) waves per CU, or four single-wave
- * rows per CU for MHA with L <= 32), so a batch of whole rows lasts at least
- * as long as its longest row. bs_attention_workspace_bytes(...) returns the
- * bytes of partial slots for a plan that cuts the longest rows into pieces of
- * 64-key tiles (each piece writes its un-normalised output, running max and
- * row sum; a merge launch combines them by log-sum-exp weights), or 0 when no
- * cut pays off (rows that already fill the GPU evenly, BS_F32, invalid
- * arguments). With
+ * once (one or two workgroups of G * ceil(L / 32) waves per CU; for MHA with
+ * L <= 32 four single-wave rows per CU, eight at D = 64), so a batch of whole
+ * rows lasts at least as long as its longest row.
+ * bs_attention_workspace_bytes(...) returns the bytes of partial slots for a
+ * plan that cuts the longest rows into pieces of 64-key tiles (each piece writes
+ * its un-normalised output, running max and row sum; a merge combines them by
+ * log-sum-exp weights), or 0 when no cut pays off (rows that already fill the
+ * GPU evenly, BS_F32, invalid arguments). With
  * ws_bytes at least that size the call runs the plan, otherwise every row
  * whole; both agree within rounding (bf16 output). The plan depends only on
  * the arguments of the size query. Calls that may overlap (different
@@ -199,9 +199,13 @@ size_t bs_attention_workspace_bytes(const bs_req_desc* reqs, int n, int L, int H
                                     bs_dtype dt);
 /*
  * Host only (no device work): the BS_BF16 attention's work list for these
- * arguments, in launch order, as 6 int32 per workgroup: request, KV head,
- * first 32-row block, first and one-past-last 64-key tile, partial slot (-1
- * for a whole row). split = 0 gives the whole-row list, 1 the split-KV plan
+ * arguments, as 6 int32 per work item: request, KV head, first 32-row block,
+ * first and one-past-last 64-key tile, partial slot (-1 for a whole row). One
+ * item is one workgroup, longest first; for MHA with L <= 32 it is one wave, and
+ * a list of N items, N a multiple of 4, is dealt to workgroups of four (items
+ * ranked b, b + N/4, b + N/2 and b + 3N/4 by length stand at 4b .. 4b + 3). Lists of
+ * up to 512 and of more than 1024 such items are launched in order of rank, in
+ * workgroups of one and two. split = 0 gives the whole-row list, 1 the split-KV plan
  * (the one bs_attention_workspace_bytes sizes). Writes min(*n_items,
  * max_items) entries to `items` (caller-owned), the list length to *n_items
  * and the plan's partial-slot count to *n_parts. BS_ERR_UNSUPPORTED outside

@@ -38,10 +38,12 @@ __device__ inline void dma16_sv(uint32_t lds, uint64_t base, uint32_t off) {
                : "memory");
 }
 
-// The same two transfers with the non-temporal hint: for tiles read exactly
-// once (the step attention's K/V stream), so they do not displace lines that
-// other work reuses. Kernels that share tiles through L2 (the output head,
-// the refresh) use the plain forms.
+// The same two transfers with the non-temporal hint: for tiles read once (the
+// step attention's K/V stream, the head matrix under a single row tile), so they
+// do not displace lines that other work reuses. Tiles shared through L2 (the
+// head matrix under several row tiles, the hidden rows, the refresh) use the
+// plain forms. The fp32 attention uses these also where several workgroups read
+// one KV head (more than 32 rows in its query group).
 __device__ inline void dma16_once(uint32_t lds, const void* gptr) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(__builtin_amdgcn_readfirstlane(lds)),
                "v"(gptr)

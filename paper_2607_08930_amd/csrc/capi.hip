@@ -327,9 +327,10 @@ int check_attention_tensors(bs_ctx* c, const void* q, const void* k_new, const v
 // the tail of the grid is made of short items: one workgroup per (request,
 // KV head), or per (request, KV head, 32-row block) when the query group
 // times the row blocks exceeds 8 waves. When one wave owns an item (G = 1,
-// L <= 32), workgroup b takes the items ranked b, b + NB, b + 2 NB, ... (NB
-// workgroups): every CU streams about the same number of bytes instead of
-// some CUs getting only the longest rows. Allocates nothing: `items` and
+// L <= 32), the list is dealt to workgroups of four: workgroup b takes the items
+// ranked b, b + NB, b + 2 NB, ... (NB workgroups), so every CU streams about the
+// same number of bytes instead of some CUs getting only the longest rows. (The
+// kernel's forms of one and two waves undo the deal.) Allocates nothing: `items` and
 // `tmp` hold attention_item_count(...) entries each.
 int attention_split(int L, int Hq, int Hkv) {
   const int RB = (L + 31) / 32;
@@ -340,9 +341,9 @@ size_t attention_item_count(int n, int L, int Hq, int Hkv, bs_dtype dt) {
   return dt == BS_BF16 ? (size_t)n * Hkv * attention_split(L, Hq, Hkv) : 0;
 }
 
-// The single-wave kernel's list (sorted longest first): workgroup b takes
-// items b, b + NB, b + 2 NB, b + 3 NB, so every workgroup holds a long and a
-// short share (only when the list fills whole workgroups).
+// The single-wave kernel's list (sorted longest first) dealt to workgroups of
+// four: workgroup b takes items b, b + NB, b + 2 NB, b + 3 NB, so every workgroup
+// holds a long and a short share (only when the list fills whole workgroups).
 void interleave_waves(AttnItem* items, AttnItem* tmp, size_t N) {
   if (N % kMhaWaves) return;
   const size_t NB = N / kMhaWaves;
@@ -376,14 +377,14 @@ void attention_items_into(AttnItem* items, AttnItem* tmp, const bs_req_desc* req
 }
 
 // ---- split-KV plan
-// The attention kernels hold a fixed number of work slots at once: the
-// shared-tile (GQA) kernel one workgroup per CU (its ring fills the LDS), the
-// single-wave (MHA) kernel four waves per CU. So a launch of whole rows lasts
-// at least as long as its longest row, while slots that drew short rows sit
-// idle: the straggler effect of a heterogeneous batch. The plan can cut rows
-// into pieces of 64-key tiles; each piece writes a partial and a merge launch
-// combines a row's pieces. Its estimate of a launch, in 64-key tiles of one
-// slot's loop, is the larger of
+// The attention kernels hold a fixed number of work slots at once. The plan
+// counts one workgroup per CU for the shared-tile (GQA) kernel (its ring fills
+// the LDS) and four waves per CU for the single-wave (MHA) kernel. A launch of
+// whole rows lasts at least as long as its longest row, while slots that drew
+// short rows sit idle: the straggler effect of a heterogeneous batch. The plan
+// can cut rows into pieces of 64-key tiles; each piece writes a partial and a
+// merge launch combines a row's pieces. Its estimate of a launch, in 64-key tiles
+// of one slot's loop, is the larger of
 //  * the list schedule: work items longest first on the least-loaded slot
 //    (what the dispatcher does with a list sorted that way), each costing
 //    kPieceOverhead + its tiles, and
@@ -401,9 +402,19 @@ void attention_items_into(AttnItem* items, AttnItem* tmp, const bs_req_desc* req
 // with none below the whole rows' estimate nothing is cut. So a batch that
 // fills the GPU with rows of similar length runs whole, and a few long rows
 // beside short ones are spread over the idle slots.
+//
+// The estimate approximates the launch: it was calibrated on single-wave items
+// placed four to a workgroup that holds its CU, and one shared-tile workgroup per
+// CU. The launch also runs one or two single-wave items to a workgroup
+// (kMhaSpread, kMhaRound) and two shared-tile workgroups to a CU
+// (pair_workgroups), and the last layer of a fused step has no merge launch of its
+// own; a cut may move a list across those lines. So for few rows the choice
+// depends on small differences of length: 5 or 6 LLaDA-8B requests run whole in
+// 160 or 192 items or in 416 to 480 pieces. Both beat four to a workgroup there (18
+// batches of 5 to 10 requests: 27-36 us before, 19-30 now).
 constexpr int kPlanCUs = 256;
 constexpr double kPieceOverhead = 2.0;
-constexpr double kMergeFixed = 3.0;        // the merge launch, in tiles
+constexpr double kMergeFixed = 3.0;        // a merge launch, in tiles
 // The merge's cost per partial read back: a partial of the shared-tile kernel
 // holds up to eight waves' output, one of the single-wave kernel one wave's.
 // Measured on LLaDA-8B heads (us of attention and merge; 0.02 for both before):
@@ -414,7 +425,7 @@ constexpr double kMergePerPartShared = 0.02;
 constexpr double kMergePerPartWave = 0.01;
 
 struct PlanShape {
-  int group;          // work items per workgroup (one workgroup per CU)
+  int group;          // work items per CU, as one workgroup
   double full_load;   // per-tile slowdown with every slot busy
   double per_part;    // merge cost of a partial
 };

@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a, int jblocks) {
 // MFMAs, so their M index m stands for feature 64 dg + 4 m + e.
 // Bound: HBM (K and V are read once per 32 query rows) with the fp32 matrix
 // rate, a sixteenth of bf16's, close behind. Measured on 8 LLaDA-8B-shaped
-// requests (32 heads, up to 733 keys, 135 MB): 46.5 us, 2.9 TB/s, against
+// requests (32 heads, up to 733 keys, 135 MB): 47.0 us, 2.9 TB/s, against
 // 778 us for the one-wave-per-row kernel above; four waves with two stages of
 // both tiles each, 55 us.
 

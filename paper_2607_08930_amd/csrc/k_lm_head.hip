@@ -116,13 +116,18 @@ __device__ inline void wait_stages(int k) {
 // 12% longer than eight.
 //
 // KS = 2 where a slice has few MFMAs between barriers (M <= 2 and d a multiple of
-// 64): 125 rows of a LLaDA-8B head 213 -> 202 us. At M = 3 and 4 it leaves two
+// 64): 125 rows of a LLaDA-8B head 206 -> 196 us (this kernel). At M = 3 and 4 it leaves two
 // stages of LDS and takes longer: 502 rows 492 -> 526, 1035 of a Dream-7B head
 // 1088 -> 1125.
 //
 // ONCE: W is read by one row tile only and streams past the L2's other lines
 // with the non-temporal hint (calls on a LLaDA-8B head: 12 rows 193 -> 174 us, 64:
-// 193 -> 177, 125: 216.7 -> 212; Dream-7B head, 52 rows: 224 -> 208).
+// 193 -> 177, 125: 216.7 -> 212; Dream-7B head, 52 rows: 224 -> 208). Matrices of
+// less than the 256 MB Infinity Cache, too: between two calls a serving program
+// streams its layers, so W comes from memory (4 requests, 32 MB: 55.5 -> 51.4, 65
+// MB: 48.0 -> 42.1, 262 MB: 105.8 -> 84.1). Called back to back with nothing between,
+// W stays in that cache and the plain form is the faster by up to a quarter
+// (65 MB: 34.7 against 32.7, 262 MB: 76.1 against 58.6).
 template <int M, bool ONCE, int KS>
 __device__ inline void lm_tile(const LmArgs& a, uint16_t* ring, int vt, int r0, int count) {
   constexpr int HB = 4 * M;                              // 1 KiB blocks (16 rows) of the H tile

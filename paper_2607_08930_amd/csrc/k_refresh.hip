@@ -24,11 +24,14 @@
 //                computes the scores of u + 1. Four sub-tiles are unrolled
 //                over the ring's slots, so LDS addresses are immediates and a
 //                sub-tile is 16 MFMAs beside 59 VALU instructions. What bounds
-//                it: MFMA and VALU issue (matrix cores busy 46% at 2.1 GHz).
-//                Measured on 64 Dream-7B-shaped rows (1.21 TFLOP): 1215 us in
-//                steady state, 1000 TFLOP/s; with per-sub-tile address
-//                arithmetic (about 40 VALU instructions more) and V fragments
-//                read right before their MFMA, 1.11x the whole call's time.
+//                it: MFMA and VALU issue on long rows (64 Dream-7B-shaped rows:
+//                matrix cores busy 46% at 1.8 GHz), each item's first tiles,
+//                queries and output on short ones (32 LLaDA-8B-shaped rows: 30%
+//                at 2.1 GHz). Measured on the former (1.17 TFLOP): 1316 us in the
+//                mean of 56 launches and 1226 in the fastest, 0.89 and 0.95 PFLOP/s;
+//                with per-sub-tile address arithmetic (about 40 VALU
+//                instructions more) and V fragments read right before their
+//                MFMA, 1.11x the whole call's time.
 #include "bs_lds.h"
 #include "bs_refresh.h"
 
