@@ -59,6 +59,8 @@ struct AttnMerge {
   int32_t part0, nparts, pad0, pad1;
 };
 
+constexpr int kMergeBatch = 8;                  // pieces whose loads a merge has in flight
+
 constexpr int kAttnTile = 64;                   // keys per tile of the shared-tile kernel
 // floats of one wave's partial at head dimension D: O^T in accumulator order
 // (D / 8 groups of 4 per lane, 64 lanes), then the running max (log2 units)
@@ -93,6 +95,7 @@ struct AttnArgs {
   const AttnMerge* merges;
   int n_merge;
   int pair;   // the items run two workgroups to a CU (where the kernel has that form)
+  int long_merge;   // a split row has more than kMergeBatch pieces
 };
 
 // Waves (independent items) per workgroup of the single-wave bf16 kernel, whose

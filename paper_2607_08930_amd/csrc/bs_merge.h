@@ -23,14 +23,21 @@ inline int merge_blocks(const AttnArgs& a) { return (a.n_merge * a.G * a.RBW * (
 // Latency bounds it, so a wave takes one group only: with a quarter of the
 // groups per wave (the max and sum of a piece read once per wave) the merge of
 // 92 rows in 224 pieces took 16.4 us instead of 10.9.
-template <int D>
+//
+// UNIFORM: the row's entry is read through scalar loads and its fields stay in
+// SGPRs. That is the faster form while every row has at most kMergeBatch pieces
+// (calls: 128 rows of 2 pieces 30.55 -> 29.9 us, 64 rows of 2-4 33.7 -> 33.0), and the
+// slower one where some rows take several batches beside many that take one (4
+// rows of 27 pieces beside 36 of 2: 32.9 -> 33.4; the merge itself 9.32 -> 9.76).
+template <int D, bool UNIFORM>
 __device__ inline void merge_rows(const AttnArgs& a, int b) {
   typedef float f32x4_t __attribute__((ext_vector_type(4)));
   constexpr int NG = D / 8;                       // groups of 4 floats per lane
   constexpr int OFL = NG * 64 * 4;
-  constexpr int CH = 8;                           // pieces per batch of loads
+  constexpr int CH = kMergeBatch;
   const int GW = a.G * a.RBW;
-  const int wv = __builtin_amdgcn_readfirstlane(b * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int wl = b * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wv = UNIFORM ? __builtin_amdgcn_readfirstlane(wl) : wl;
   if (wv >= a.n_merge * GW * NG) return;
   const int k = wv % NG, wg = (wv / NG) % GW;
   const AttnMerge mg = a.merges[wv / (NG * GW)];

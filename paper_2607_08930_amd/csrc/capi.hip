@@ -39,7 +39,7 @@ struct Slot {
   size_t cap = 0;
   std::vector<unsigned char> key;
   uint64_t hash = 0;
-  int meta[7] = {0, 0, 0, 0, 0, 0, 0};  // blob layout (offsets, counts) recorded at build time
+  int meta[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // blob layout (offsets, counts) recorded at build time
   hipEvent_t ready = nullptr;  // recorded after the upload
   hipEvent_t done = nullptr;   // recorded after the last launch that read it
   hipStream_t stream = nullptr;
@@ -153,7 +153,7 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 // Blob = descriptors followed by an optional work list, 16-byte aligned parts.
 struct Blob {
   std::vector<unsigned char> bytes;
-  int meta[7] = {0, 0, 0, 0, 0, 0, 0};
+  int meta[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   size_t add(const void* p, size_t n) {
     size_t off = (bytes.size() + 15) & ~size_t(15);
     bytes.resize(off + n);
@@ -596,7 +596,7 @@ size_t part_bytes(int parts, int L, int Hq, int Hkv, int D) {
 }
 
 // Descriptors, then (bf16) the work items above, then (split) the merge list;
-// meta = {descriptors, items, item count, merges, merge count, partial slots, pair_workgroups}.
+// meta = {descriptors, items, item count, merges, merge count, partial slots, pair_workgroups, long_merge}.
 void attention_blob(Blob& blob, const bs_req_desc* reqs, int n, int L, int Hq, int Hkv, bs_dtype dt, bool split) {
   blob.meta[0] = (int)blob.add(reqs, sizeof(bs_req_desc) * n);
   if (dt == BS_BF16) {
@@ -619,6 +619,7 @@ void attention_blob(Blob& blob, const bs_req_desc* reqs, int n, int L, int Hq, i
     blob.meta[4] = (int)merges.size();
     blob.meta[5] = parts;
     blob.meta[6] = pair_workgroups(list.data(), list.size()) ? 1 : 0;
+    for (const AttnMerge& m : merges) blob.meta[7] |= m.nparts > kMergeBatch;
   }
 }
 
@@ -634,6 +635,7 @@ AttnArgs attention_args(const void* dblob, const int* meta, int L, int Hq, int H
   a.merges = reinterpret_cast<const AttnMerge*>(base + meta[3]);
   a.n_merge = meta[4];
   a.pair = meta[6];
+  a.long_merge = meta[7];
   a.parts = static_cast<float*>(parts);
   a.L = L; a.Hq = Hq; a.Hkv = Hkv; a.D = D; a.G = Hq / Hkv; a.RB = (L + 31) / 32; a.R = R; a.W = W;
   a.RBW = a.G * a.RB > 8 ? 1 : a.RB;
@@ -1404,7 +1406,7 @@ int bs_mixed_state_step_noalloc(bs_ctx* c, const bs_req_desc* reqs, int n, int L
   std::memcpy(h, reqs, sizeof(bs_req_desc) * n);
   if (n_items) attention_items_into(reinterpret_cast<AttnItem*>(h + items_off), sp.tmp.get(), reqs, n, L, Hq, Hkv);
   const int pair = n_items && pair_workgroups(reinterpret_cast<const AttnItem*>(h + items_off), n_items) ? 1 : 0;
-  const int meta[7] = {0, (int)items_off, (int)n_items, 0, 0, 0, pair};   // whole rows: no merge list
+  const int meta[8] = {0, (int)items_off, (int)n_items, 0, 0, 0, pair, 0};   // whole rows: no merge list
   hipError_t e = hipMemcpyAsync(dscratch, h, blob_bytes, hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return hip_fail(c, e, "hipMemcpyAsync(scratch)");
   e = hipEventRecord(sp.copied[k], s);

@@ -1096,9 +1096,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16_pair(AttnArgs a) {
 }
 
 // Split-KV merge as a launch of its own (merge_rows; launched at 256 threads).
-template <int D>
+template <int D, bool UNIFORM>
 __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
-  merge_rows<D>(a, blockIdx.x);
+  merge_rows<D, UNIFORM>(a, blockIdx.x);
 }
 
 template <int D>
@@ -1122,8 +1122,12 @@ hipError_t launch_bf16_d(const AttnArgs& a, int GW, bool merge, hipStream_t s) {
   } else {
     hipLaunchKernelGGL((k_attn_bf16_group<D, 4, 4>), dim3(a.n_items), dim3(64 * GW), 0, s, a);
   }
-  if (merge && a.n_merge > 0)
-    hipLaunchKernelGGL((k_attn_merge<D>), dim3((unsigned)merge_blocks(a)), dim3(256), 0, s, a);
+  if (merge && a.n_merge > 0) {
+    if (a.long_merge)
+      hipLaunchKernelGGL((k_attn_merge<D, false>), dim3((unsigned)merge_blocks(a)), dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_attn_merge<D, true>), dim3((unsigned)merge_blocks(a)), dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 

@@ -349,7 +349,7 @@ template <typename T, int D>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_decode_parts_merge(DecArgs a, AttnArgs m,
                                                                                                    int nmerge) {
   if ((int)blockIdx.x < nmerge)
-    merge_rows<D>(m, blockIdx.x);
+    merge_rows<D, true>(m, blockIdx.x);   // beside the row stream the other form is no faster
   else
     decode_part<T>(a, blockIdx.x - nmerge);
 }

@@ -664,6 +664,21 @@ def test_attention_split_kv_stragglers(ctx):
         _att(ctx, w, f"{label} stragglers")
 
 
+@pytest.mark.parametrize("L,Hq,Hkv,D,p8", [(32, 28, 4, 128, 896), (64, 4, 4, 64, 832), (32, 8, 8, 128, 896),
+                                           (16, 8, 8, 64, 896)])
+def test_attention_split_kv_piece_counts(ctx, L, Hq, Hkv, D, p8):
+    # the merge loads a row's pieces eight at a time, and has a form for lists
+    # whose rows all have at most eight: longest rows of 8, 9 (one piece in a
+    # second batch) and 17 pieces, beside a short one
+    _, bs, _ = lazy()
+    for pieces in (8, 9, 17):
+        w = synth.custom(L, Hq, Hkv, D, 10, "bf16", [p8 + 128 * (pieces - 8), 40], [2 * L, 2 * L], [1, 0],
+                         kv_sigma=0.1, q_sigma=3.0)
+        _, per_row = _rows_cut(bs, w)
+        assert max(per_row.values()) == pieces
+        _att(ctx, w, f"L{L} G{Hq // Hkv} D{D} {pieces} pieces")
+
+
 def test_attention_rejects_unsupported(ctx):
     torch, bs, _ = lazy()
     w = synth.custom(32, 36, 4, 128, 10, "bf16", [3], [64], [0])   # 9 query heads per KV head > 8 waves
