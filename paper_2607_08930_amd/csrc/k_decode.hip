@@ -342,16 +342,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 }
 
 // The row reductions of a fused step whose last attention has split rows: the
-// first workgroups merge those (neither reads what the other writes), so the
-// step has one launch fewer and the merge's latency passes under the row stream:
-// a step of one LLaDA-8B-shaped request (32 split rows) 31.7 -> 28.7 us.
+// last workgroups merge those (neither reads what the other writes), so the
+// step has one launch fewer and the merge's latency passes under the row stream.
+// Steps, with a merge launch of its own -> so (us): one LLaDA-8B-shaped request
+// (32 split rows) 26.2 -> 23.1, Dream-7B batches of 8 (32 rows) 47.3 -> 42.0, 24
+// 68.1 -> 64.5, 77 skewed 121.6 -> 122.0. With the merge in the first workgroups
+// the row stream waited for their places: 23.0, 46.5, 68.5 and 122.4.
 template <typename T, int D>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_decode_parts_merge(DecArgs a, AttnArgs m,
                                                                                                    int nmerge) {
-  if ((int)blockIdx.x < nmerge)
-    merge_rows<D, true>(m, blockIdx.x);   // beside the row stream the other form is no faster
+  const int rows = (int)gridDim.x - nmerge;
+  if ((int)blockIdx.x >= rows)
+    merge_rows<D, true>(m, blockIdx.x - rows);   // beside the row stream the other form is no faster
   else
-    decode_part<T>(a, blockIdx.x - nmerge);
+    decode_part<T>(a, blockIdx.x);
 }
 
 __global__ __launch_bounds__(64) void k_decode_select(DecArgs a) {
