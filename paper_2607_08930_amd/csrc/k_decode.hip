@@ -252,8 +252,10 @@ __device__ inline void stream_part(const T* x, int c0, int V, int tid, RowAcc& r
   }
 }
 
+// `block` is unsigned like blockIdx.x: a signed division here made the row
+// reductions 1% longer (L = 64, 8 requests: 16.7 -> 17.0 us).
 template <typename T>
-__device__ inline void decode_part(const DecArgs& a, int block) {
+__device__ inline void decode_part(const DecArgs& a, unsigned block) {
   constexpr int N = Lanes<T>::N;
   constexpr int CH = kDecChunkBytes / sizeof(T);
   static_assert(kDecPartChunks >= 1 && kDecPartChunks <= 4, "stream_part is instantiated for 1..4 chunks");
