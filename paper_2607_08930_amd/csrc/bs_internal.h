@@ -95,7 +95,7 @@ struct AttnArgs {
   const AttnMerge* merges;
   int n_merge;
   int pair;   // the items run two workgroups to a CU (where the kernel has that form)
-  int long_merge;   // a split row has more than kMergeBatch pieces
+  int long_merge;   // a split row has more than two batches of pieces (2 kMergeBatch)
 };
 
 // Waves (independent items) per workgroup of the single-wave bf16 kernel, whose

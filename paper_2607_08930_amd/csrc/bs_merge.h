@@ -25,10 +25,11 @@ inline int merge_blocks(const AttnArgs& a) { return (a.n_merge * a.G * a.RBW * (
 // 92 rows in 224 pieces took 16.4 us instead of 10.9.
 //
 // UNIFORM: the row's entry is read through scalar loads and its fields stay in
-// SGPRs. That is the faster form while every row has at most kMergeBatch pieces
-// (calls: 128 rows of 2 pieces 30.55 -> 29.9 us, 64 rows of 2-4 33.7 -> 33.0), and the
-// slower one where some rows take several batches beside many that take one (4
-// rows of 27 pieces beside 36 of 2: 32.9 -> 33.4; the merge itself 9.32 -> 9.76).
+// SGPRs. That is the faster form while rows have few pieces (calls: 128 rows of 2
+// 30.55 -> 29.9 us, 64 rows of 2-4 33.7 -> 33.0, 8 rows of 11 beside 80 of 2: 45.1 ->
+// 44.4), and the slower one where some rows take several batches beside many
+// that take one (4 rows of 27 beside 36 of 2: 32.9 -> 33.4; the merge itself 9.32
+// -> 9.76). Few rows of 15 pieces: the same in both.
 template <int D, bool UNIFORM>
 __device__ inline void merge_rows(const AttnArgs& a, int b) {
   typedef float f32x4_t __attribute__((ext_vector_type(4)));

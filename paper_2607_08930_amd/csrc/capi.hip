@@ -619,7 +619,7 @@ void attention_blob(Blob& blob, const bs_req_desc* reqs, int n, int L, int Hq, i
     blob.meta[4] = (int)merges.size();
     blob.meta[5] = parts;
     blob.meta[6] = pair_workgroups(list.data(), list.size()) ? 1 : 0;
-    for (const AttnMerge& m : merges) blob.meta[7] |= m.nparts > kMergeBatch;
+    for (const AttnMerge& m : merges) blob.meta[7] |= m.nparts > 2 * kMergeBatch;
   }
 }
 

@@ -343,21 +343,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   decode_part<T>(a, blockIdx.x);
 }
 
-// The row reductions of a fused step whose last attention has split rows: the
-// last workgroups merge those (neither reads what the other writes), so the
-// step has one launch fewer and the merge's latency passes under the row stream.
-// Steps, with a merge launch of its own -> so (us): one LLaDA-8B-shaped request
-// (32 split rows) 26.2 -> 23.1, Dream-7B batches of 8 (32 rows) 47.3 -> 42.0, 24
-// 68.1 -> 64.5, 77 skewed 121.6 -> 122.0. With the merge in the first workgroups
-// the row stream waited for their places: 23.0, 46.5, 68.5 and 122.4.
+// The row reductions of a fused step whose last attention has split rows: nmerge
+// workgroups from merge0 on merge those (neither reads what the other writes),
+// so the step has one launch fewer and the merge's latency passes under the row
+// stream. They stand last, so that the row stream does not wait for their places,
+// but first while they are few (kMergeFirst): then they take an eighth of the
+// chip's places at most, and a row of many pieces is not left to the end. Steps
+// (us; a merge launch of its own, first, last): one LLaDA-8B-shaped request (128
+// workgroups) 26.2, 23.0, 23.1; a Dream-7B straggler row of 26 pieces among 8
+// short rows (112) 44.3, 38.0, 39.8, of 43 pieces among 6 (64) 39.2, 33.8, 34.7;
+// Dream-7B batches of 8 (896) 47.3, 46.3, 41.9, 24 (2688) 68.0, 67.9, 64.2, 40 with a
+// straggler 98.2, 98.9, 96.0.
+constexpr int kMergeFirst = 128;
+
 template <typename T, int D>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_decode_parts_merge(DecArgs a, AttnArgs m,
-                                                                                                   int nmerge) {
-  const int rows = (int)gridDim.x - nmerge;
-  if ((int)blockIdx.x >= rows)
-    merge_rows<D, true>(m, blockIdx.x - rows);   // beside the row stream the other form is no faster
+                                                                                                   int nmerge, int merge0) {
+  const int b = (int)blockIdx.x - merge0;
+  if (b >= 0 && b < nmerge)
+    merge_rows<D, true>(m, b);   // beside the row stream the other form is no faster
   else
-    decode_part<T>(a, blockIdx.x);
+    decode_part<T>(a, merge0 ? blockIdx.x : blockIdx.x - nmerge);
 }
 
 __global__ __launch_bounds__(64) void k_decode_select(DecArgs a) {
@@ -370,13 +376,13 @@ namespace {
 template <typename T>
 hipError_t launch_rows(const DecArgs& a, const AttnArgs* merge, hipStream_t s) {
   const unsigned rows = (unsigned)((int64_t)a.n * a.L * a.parts);
-  const int nm = merge ? merge_blocks(*merge) : 0;
+  const int nm = merge ? merge_blocks(*merge) : 0, m0 = nm <= kMergeFirst ? 0 : (int)rows;
   if (nm == 0)
     hipLaunchKernelGGL(k_decode_parts<T>, dim3(rows), dim3(kThreads), 0, s, a);
   else if (merge->D == 128)
-    hipLaunchKernelGGL((k_decode_parts_merge<T, 128>), dim3(nm + rows), dim3(kThreads), 0, s, a, *merge, nm);
+    hipLaunchKernelGGL((k_decode_parts_merge<T, 128>), dim3(nm + rows), dim3(kThreads), 0, s, a, *merge, nm, m0);
   else
-    hipLaunchKernelGGL((k_decode_parts_merge<T, 64>), dim3(nm + rows), dim3(kThreads), 0, s, a, *merge, nm);
+    hipLaunchKernelGGL((k_decode_parts_merge<T, 64>), dim3(nm + rows), dim3(kThreads), 0, s, a, *merge, nm, m0);
   return hipGetLastError();
 }
 }  // namespace

@@ -668,10 +668,10 @@ def test_attention_split_kv_stragglers(ctx):
                                            (16, 8, 8, 64, 896)])
 def test_attention_split_kv_piece_counts(ctx, L, Hq, Hkv, D, p8):
     # the merge loads a row's pieces eight at a time, and has a form for lists
-    # whose rows all have at most eight: longest rows of 8, 9 (one piece in a
-    # second batch) and 17 pieces, beside a short one
+    # whose rows all have at most 16: longest rows of 8, 9 (one piece in a second
+    # batch), 16 and 17 pieces, beside a short one
     _, bs, _ = lazy()
-    for pieces in (8, 9, 17):
+    for pieces in (8, 9, 16, 17):
         w = synth.custom(L, Hq, Hkv, D, 10, "bf16", [p8 + 128 * (pieces - 8), 40], [2 * L, 2 * L], [1, 0],
                          kv_sigma=0.1, q_sigma=3.0)
         _, per_row = _rows_cut(bs, w)

@@ -178,6 +178,32 @@ def test_fused_step_split_kv_stragglers(ctx, Hq, Hkv):
         check_attention(w, la["out"], oracle.widen(lc["out"], w.dtype), label="split vs whole rows")
 
 
+@pytest.mark.parametrize("H,D", [(32, 128), (33, 128), (64, 64), (65, 64)])
+def test_fused_step_place_of_the_merge(ctx, H, D):
+    """One request whose H rows are all cut: their merge takes H D / 32
+    workgroups, the first of the row reductions' launch up to 128 (H = 32, 64) and
+    the last beyond (33, 65). Either equals the separate calls byte for byte."""
+    torch, bs, bstep = lazy()
+    w = synth.custom(32, H, H, D, 3000, "bf16", [700], [64], [1], variant=5, kv_sigma=D ** -0.5)
+    items, _ = bs.bs_attention_work_list(w.reqs, w.L, w.Hq, w.Hkv, w.D, bs.BS_BF16, 1)
+    cut = {tuple(x[:3]) for x in items.tolist() if x[5] >= 0}
+    assert len(cut) == H
+    say(f"[fused step, merge of {H} rows, D={D}]")
+    a, host = make_state(w)
+    b, _ = make_state(w)
+    bstep.run_step(ctx, a, w.reqs, want_conf=True, fused=True)
+    bstep.run_step(ctx, b, w.reqs, want_conf=True, fused=False)
+    torch.cuda.synchronize()
+    ga, gb = snapshot(a), snapshot(b)
+    ref = oracle.mixed_state_step(w.reqs, w.L, host["tokens"], host["mask"], host["layers"], host["logits"],
+                                  tau=w.tau, q_min=w.q_min, eos_id=w.eos_id, dtype=w.dtype)
+    check_step(w, ga, ref, host, f"merge of {H} rows")
+    for key in ("tokens", "mask", "pos", "conf", "n_unmasked", "done", "eos_seen"):
+        np.testing.assert_array_equal(ga[key], gb[key], err_msg=key)
+    for key in ("out", "k_cache", "v_cache"):
+        np.testing.assert_array_equal(ga["layers"][0][key], gb["layers"][0][key], err_msg=key)
+
+
 @pytest.mark.parametrize("L,Hq,Hkv,D", [(32, 4, 4, 64), (32, 4, 4, 128), (64, 14, 2, 64), (48, 14, 2, 128)])
 def test_fused_step_split_rows_in_each_layer(ctx, L, Hq, Hkv, D):
     # split rows of the first layer are merged by a launch of their own, those
