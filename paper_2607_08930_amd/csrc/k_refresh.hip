@@ -27,8 +27,8 @@
 //                it: MFMA and VALU issue on long rows (64 Dream-7B-shaped rows:
 //                matrix cores busy 46% at 1.8 GHz), each item's first tiles,
 //                queries and output on short ones (32 LLaDA-8B-shaped rows: 30%
-//                at 2.1 GHz). Measured on the former (1.17 TFLOP): 1316 us in the
-//                mean of 56 launches and 1226 in the fastest, 0.89 and 0.95 PFLOP/s;
+//                at 2.1 GHz). Measured on the former (1.17 TFLOP): 1.3 ms in
+//                the mean of 56 launches and 1.2 in the fastest, 0.9 PFLOP/s;
 //                with per-sub-tile address arithmetic (about 40 VALU
 //                instructions more) and V fragments read right before their
 //                MFMA, 1.11x the whole call's time.
